@@ -318,6 +318,40 @@ template <int L, int P> struct TwLds {
   }
 };
 
+// Stage twiddles of long lines (TWP 3).  The last stage of an 8192- or
+// 16384-point line has 8192 or 16384 factors W^{k r}, each used once per
+// line: as a table they are 64 or 128 KB, as much as the line itself, which
+// neither fits in LDS beside the line nor is cheap to read from L2.  With
+// k = (k1 << H) + k0, W^{k r} = W^{(k1 << H) r} W^{k0 r}: two tables of about
+// sqrt(NS) rows of R factors, both rows of the stage table, and one complex
+// multiply per factor.  Stages of up to 32 rows keep their table.
+template <int L, int P> struct TwFac {
+  using S = Sched<L, P>;
+  static constexpr int H_MIN_NS = 64;
+  __host__ __device__ static constexpr bool split(int s) { return S::ns(s) >= H_MIN_NS; }
+  __host__ __device__ static constexpr int h(int s) { return (ilog2(S::ns(s)) + 1) / 2; }
+  __host__ __device__ static constexpr int rp(int s) { return S::radix(s) >= 4 ? S::radix(s) + 1 : S::radix(s); }
+  __host__ __device__ static constexpr int rows(int s) {
+    return split(s) ? (1 << h(s)) + (S::ns(s) >> h(s)) : S::ns(s);
+  }
+  __host__ __device__ static constexpr int off(int s) { return s <= 1 ? 0 : off(s - 1) + rows(s - 1) * rp(s - 1); }
+  static constexpr int SIZE = off(S::S) > 0 ? off(S::S) : 1;
+  template <int s = 1>
+  __device__ __forceinline__ static void copy(float2* dst, const float2* __restrict__ src, int tid, int nt) {
+    if constexpr (s < S::S) {
+      constexpr int R = S::radix(s);
+      for (int i = tid; i < rows(s) * R; i += nt) {
+        const int row = i / R, r = i % R;
+        int k = row;
+        if constexpr (split(s))
+          if (row >= (1 << h(s))) k = (row - (1 << h(s))) << h(s);
+        dst[off(s) + row * rp(s) + r] = src[S::off(s) + k * R + r];
+      }
+      copy<s + 1>(dst, src, tid, nt);
+    }
+  }
+};
+
 // ---------------------------------------------------------------------------
 // LDS exchange between two stages.  Lane (m, t) holds the previous stage's
 // outputs in v[b + r*NB] destined for positions o0[b] + r*NS of line m; after
@@ -406,10 +440,18 @@ struct Stage {
           const int e = k * r * SC;
           x[r] = cmul(x[r], cmul(twt[e & ((1 << LA) - 1)], twt[(1 << LA) + (e >> LA)]));
         }
+      } else if constexpr (s > 0 && TWP == 3 && TwFac<L, P>::split(s)) {
+        using TF = TwFac<L, P>;
+        constexpr int H = TF::h(s);
+        const float2* lo = twt + TF::off(s) + (k & ((1 << H) - 1)) * TF::rp(s);
+        const float2* hi = twt + TF::off(s) + ((1 << H) + (k >> H)) * TF::rp(s);
+#pragma unroll
+        for (int r = 1; r < R; ++r) x[r] = cmul(x[r], cmul(hi[r], lo[r]));
       } else if constexpr (s > 0) {
-        // TWP 0: global table; TWP 1: LDS copy with padded rows
-        const float2* tw = TWP == 0 ? twt + S::off(s) + k * R
-                                    : twt + TwLds<L, P>::off(s) + k * TwLds<L, P>::rp(s);
+        // TWP 0: global table; TWP 1 and 3: LDS copy with padded rows
+        const float2* tw = TWP == 0   ? twt + S::off(s) + k * R
+                           : TWP == 3 ? twt + TwFac<L, P>::off(s) + k * TwFac<L, P>::rp(s)
+                                      : twt + TwLds<L, P>::off(s) + k * TwLds<L, P>::rp(s);
 #pragma unroll
         for (int r = 1; r < R; ++r) x[r] = cmul(x[r], tw[r]);
       }
@@ -570,9 +612,15 @@ k_strip(PassArgs a) {
 // once), since waiting on any later global load would also wait for the
 // prefetch.  Same lane mappings, stages and outputs as k_strip.
 // ---------------------------------------------------------------------------
+// Lines beyond 4096 points hold their stage twiddles as factors (TwFac).
+template <int L> constexpr int kPipeTwp = L > 4096 ? 3 : 1;
+template <int L, int P>
+__host__ __device__ constexpr int pipe_tw_entries() {
+  return kPipeTwp<L> == 3 ? TwFac<L, P>::SIZE : TwLds<L, P>::SIZE;
+}
 template <int L, int P, int W, int EX, bool TWID>
 __host__ __device__ constexpr int pipe_lds_entries() {
-  return (EX == 0 ? W * LdsLayout<L>::LS : (W * LdsLayout<L>::LS + 1) / 2) + TwLds<L, P>::SIZE +
+  return (EX == 0 ? W * LdsLayout<L>::LS : (W * LdsLayout<L>::LS + 1) / 2) + pipe_tw_entries<L, P>() +
          (TWID ? W * (Sched<L, P>::PP + 2) : 0);
 }
 
@@ -589,7 +637,7 @@ k_pipe(PassArgs a) {
   __shared__ float2 lds[pipe_lds_entries<L, P, W, EX, TWID>()];
   float2* xch = lds;
   float2* twl = lds + XN;
-  float2* rowl = lds + XN + TwLds<L, P>::SIZE;
+  float2* rowl = lds + XN + pipe_tw_entries<L, P>();
 
   int tid = threadIdx.x;
   int m_ld, t_ld, m_st, t_st;
@@ -607,7 +655,10 @@ k_pipe(PassArgs a) {
   const uint32_t sgn_in = a.conj_in ? 0x80000000u : 0u;
   const uint32_t sgn_out = a.conj_out ? 0x80000000u : 0u;
 
-  TwLds<L, P>::copy(twl, a.tw, tid, NT);
+  if constexpr (kPipeTwp<L> == 3)
+    TwFac<L, P>::copy(twl, a.tw, tid, NT);
+  else
+    TwLds<L, P>::copy(twl, a.tw, tid, NT);
 
   // registers of a prefetched tile; 16-bit pairs stay in their storage type
   // (one register each) until they are converted when the tile is consumed.
@@ -682,7 +733,7 @@ k_pipe(PassArgs a) {
     if (ahead < a.total_tiles) prefetch(n, ahead);
 
     int m = m_ld, t = t_ld;
-    run_stages<L, P, W, EX, 1>(v, xch, m, t, m_st, t_st, LOADM != STOREM, twl);
+    run_stages<L, P, W, EX, kPipeTwp<L>>(v, xch, m, t, m_st, t_st, LOADM != STOREM, twl);
     if (TWID) lds_barrier();  // step rows visible (also when no exchange ran)
 
     const int tib = (int)(tile - bat * a.tiles_per_batch);

@@ -104,6 +104,73 @@ bool pow2(int64_t v) { return v >= 1 && (v & (v - 1)) == 0; }
 size_t esize(int dtype) { return dtype == FFT_C64 ? 8 : 4; }
 
 // ---------------------------------------------------------------------------
+// Which variant runs a pass, by role, length and storage: the first entry
+// whose tiles are no wider than the lines and number at least `min_tiles`
+// over the whole launch.  Times below are of one pass over 2^24 points on 256
+// CUs unless another size is given (at the copy rate of 5.4 TB/s: 49.7 us in
+// complex64, 24.9 us in 16-bit storage).
+//
+// Rows (contiguous lines): 8 points per lane and 256 lanes a workgroup, so
+// that 32 waves are resident per CU and one workgroup's loads overlap
+// another's butterflies (1024 points, complex64: 53 us against 69 with 16
+// points per lane and 512 lanes; fp16: 35 against 48).  Rows of 1024 to 4096
+// complex64 points with at least 8 tiles per CU: persistent, the next tile in
+// flight (51-54 against 53-58 us; with 2 tiles per CU it is the other way
+// round, 12.5 against 10.4 us for 2^21 points).  Longer rows hold one line per
+// workgroup; their stage twiddles come from factor tables in LDS and the next
+// line is in flight (16384: 82 us against 116).  Short rows take 512 lanes.
+// ---------------------------------------------------------------------------
+struct Pref {
+  int role, bits, L;  // bits: storage of one component, 32 or 16
+  int P, W, persistent, ex;
+  int64_t min_tiles;
+};
+constexpr int64_t kCus = 256;  // MI355X
+constexpr Pref kPrefs[] = {
+    {ROLE_ROW, 32, 16, 8, 256, 0, 0, 0},
+    {ROLE_ROW, 32, 32, 8, 128, 0, 0, 0},
+    {ROLE_ROW, 32, 64, 8, 32, 0, 0, 0},
+    {ROLE_ROW, 32, 128, 8, 16, 0, 0, 0},
+    {ROLE_ROW, 32, 256, 8, 8, 0, 0, 0},
+    {ROLE_ROW, 32, 512, 8, 4, 0, 0, 0},
+    {ROLE_ROW, 32, 1024, 16, 4, 1, 0, 8 * kCus},
+    {ROLE_ROW, 32, 1024, 8, 2, 0, 0, 0},
+    {ROLE_ROW, 32, 2048, 16, 2, 1, 0, 8 * kCus},
+    {ROLE_ROW, 32, 2048, 8, 1, 0, 0, 0},
+    {ROLE_ROW, 32, 4096, 16, 1, 1, 0, 8 * kCus},
+    {ROLE_ROW, 32, 4096, 8, 1, 0, 0, 0},
+    {ROLE_ROW, 32, 8192, 16, 1, 1, 0, 0},
+    {ROLE_ROW, 32, 16384, 32, 1, 1, 0, 0},
+    {ROLE_ROW, 16, 16, 8, 256, 0, 0, 0},
+    {ROLE_ROW, 16, 32, 8, 128, 0, 0, 0},
+    {ROLE_ROW, 16, 64, 8, 32, 0, 0, 0},
+    {ROLE_ROW, 16, 128, 8, 16, 0, 0, 0},
+    {ROLE_ROW, 16, 256, 8, 8, 0, 0, 0},
+    {ROLE_ROW, 16, 512, 8, 4, 0, 0, 0},
+    {ROLE_ROW, 16, 1024, 8, 2, 0, 0, 0},
+    {ROLE_ROW, 16, 2048, 8, 1, 0, 0, 0},
+    {ROLE_ROW, 16, 4096, 8, 1, 0, 0, 0},
+    {ROLE_ROW, 16, 8192, 8, 1, 0, 0, 0},
+    {ROLE_ROW, 16, 16384, 32, 1, 0, 1, 0},
+};
+
+// The preferred variant of a pass over `batches` sets of `lines` lines, or
+// the general choice of pick() for lengths the table leaves out and for fewer
+// lines than its tiles are wide.  Contiguous lines may be fewer than a tile.
+const Variant* preferred(int role, int L, int dtype, int want_w, int64_t lines, int64_t batches) {
+  for (const Pref& f : kPrefs) {
+    if (f.role != role || f.L != L || f.bits != (dtype == FFT_C64 ? 32 : 16)) continue;
+    if (role != ROLE_ROW && f.W > lines) continue;
+    if ((lines + f.W - 1) / f.W * batches < f.min_tiles) continue;
+    for (const Variant& v : variants())
+      if (v.role == role && v.L == L && v.dtype == dtype && v.P == std::min(f.P, L) && v.W == f.W &&
+          v.persistent == f.persistent && v.ex == f.ex)
+        return &v;
+  }
+  return pick(role, L, dtype, want_w, lines);
+}
+
+// ---------------------------------------------------------------------------
 // schedule (host-only description of the launches)
 // ---------------------------------------------------------------------------
 enum Sel { SEL_IN = 0, SEL_OUT = 1, SEL_WS = 2 };
@@ -219,8 +286,10 @@ int parse_schedule(const char* s, Overrides* o) {
   return FFT_OK;
 }
 
-// Resolve an override name (must match role, L and dtype) or pick a default.
-int choose(const std::string& name, int role, int L, int dtype, int want_w, int64_t lines,
+// Resolve an override name (must match role, L and dtype) or pick a default
+// for `batches` sets of `lines` lines (0: the plan needs whole tiles of about
+// `want_w` lines).
+int choose(const std::string& name, int role, int L, int dtype, int want_w, int64_t lines, int64_t batches,
            const Variant** out) {
   if (!name.empty()) {
     const Variant* v = find_by_name(name);
@@ -228,7 +297,7 @@ int choose(const std::string& name, int role, int L, int dtype, int want_w, int6
     *out = v;
     return FFT_OK;
   }
-  *out = pick(role, L, dtype, want_w, lines);
+  *out = batches ? preferred(role, L, dtype, want_w, lines, batches) : pick(role, L, dtype, want_w, lines);
   return *out ? FFT_OK : FFT_ERR_UNSUPPORTED_SIZE;
 }
 
@@ -258,11 +327,11 @@ int build_three_pass_1d(int64_t N, int64_t batch, int dtype, const Overrides& ov
   const int64_t N1 = (int64_t)1 << l1, N2 = (int64_t)1 << l2, N3 = (int64_t)1 << l3;
   const int64_t M = N2 * N3;
   PassSpec A, C, B;
-  int rc = choose(ov.a, ROLE_SPLIT_A, (int)N1, dtype, 16, M, &A.v);
+  int rc = choose(ov.a, ROLE_SPLIT_A, (int)N1, dtype, 16, M, batch, &A.v);
   if (rc) return rc;
-  rc = choose(ov.colt, ROLE_COL_TW, (int)N2, dtype, 64, N3 * N1, &C.v);
+  rc = choose(ov.colt, ROLE_COL_TW, (int)N2, dtype, 64, N3 * N1, batch, &C.v);
   if (rc) return rc;
-  rc = choose(ov.b.empty() ? ov.col : ov.b, ROLE_COL, (int)N3, dtype, 16, N1, &B.v);
+  rc = choose(ov.b.empty() ? ov.col : ov.b, ROLE_COL, (int)N3, dtype, 16, N1, N2, &B.v);
   if (rc) return rc;
   if (M > INT32_MAX || N3 * N1 > INT32_MAX) return FFT_ERR_UNSUPPORTED_SIZE;
   PassArgs& a = A.args;
@@ -332,11 +401,11 @@ int build_three_pass_2d(int64_t R, int64_t C, int64_t batch, int dtype, const Ov
   const int64_t Sq = (int64_t)1 << (lgR / 2);
   if (Sq * C > INT32_MAX || R * batch > INT32_MAX) return FFT_ERR_UNSUPPORTED_SIZE;
   PassSpec c1, c2, rw;
-  int rc = choose(ov.colt, ROLE_COL_TW, (int)Sq, dtype, 64, C, &c1.v);
+  int rc = choose(ov.colt, ROLE_COL_TW, (int)Sq, dtype, 64, C, 0, &c1.v);
   if (rc) return rc;
-  rc = choose(ov.col, ROLE_COL, (int)Sq, dtype, 64, C, &c2.v);
+  rc = choose(ov.col, ROLE_COL, (int)Sq, dtype, 64, C, 0, &c2.v);
   if (rc) return rc;
-  rc = choose(ov.row, ROLE_ROW, (int)C, dtype, 2, R, &rw.v);
+  rc = choose(ov.row, ROLE_ROW, (int)C, dtype, 2, R, 0, &rw.v);
   if (rc) return rc;
   // row tiles of an even number of rows never split a transpose pair (the
   // map lists the pairs first, then the diagonal rows), and whole tiles
@@ -430,7 +499,7 @@ int build_schedule_inner(const int64_t* n, int64_t batch, int dims, int dtype, c
       S.passes.push_back(p);
     } else if (l <= kSingleMaxLog2 && ov.split == 0) {
       PassSpec p;
-      int rc = choose(ov.single.empty() ? ov.row : ov.single, ROLE_ROW, (int)N, dtype, 64, batch, &p.v);
+      int rc = choose(ov.single.empty() ? ov.row : ov.single, ROLE_ROW, (int)N, dtype, 64, batch, 1, &p.v);
       if (rc) return rc;
       PassArgs& a = p.args;
       a.in_batch = a.out_batch = 0;
@@ -450,9 +519,9 @@ int build_schedule_inner(const int64_t* n, int64_t batch, int dims, int dtype, c
       S.split[0] = N1;
       S.split[1] = N2;
       PassSpec A, B;
-      int rc = choose(ov.a, ROLE_SPLIT_A, (int)N1, dtype, 16, N2, &A.v);
+      int rc = choose(ov.a, ROLE_SPLIT_A, (int)N1, dtype, 16, N2, batch, &A.v);
       if (rc) return rc;
-      rc = choose(ov.b.empty() ? ov.col : ov.b, ROLE_COL, (int)N2, dtype, 16, N1, &B.v);
+      rc = choose(ov.b.empty() ? ov.col : ov.b, ROLE_COL, (int)N2, dtype, 16, N1, batch, &B.v);
       if (rc) return rc;
       // pass A: x viewed as [N1][N2]; line n2 (column), point n1; writes
       // T[n2*N1 + k1] times W_N^{n2*k1}.
@@ -518,7 +587,7 @@ int build_schedule_inner(const int64_t* n, int64_t batch, int dims, int dtype, c
       }
       if (f.v->W != r) return FFT_ERR_INVALID_ARGUMENT;
       int rc;
-      rc = choose(ov.col, ROLE_COL, (int)M, dtype, 16, C, &cl.v);
+      rc = choose(ov.col, ROLE_COL, (int)M, dtype, 16, C, r, &cl.v);
       if (rc) return rc;
       if (M * batch > INT32_MAX) return FFT_ERR_UNSUPPORTED_SIZE;
       PassArgs& a = f.args;
@@ -558,9 +627,9 @@ int build_schedule_inner(const int64_t* n, int64_t batch, int dims, int dtype, c
       // pass -> out): every column tile then reads one contiguous block
       if (ov.col3 == 1 || R < 2 || C < ov.blk || C % ov.blk) return FFT_ERR_INVALID_ARGUMENT;
       PassSpec rw, cl;
-      int rc = choose(ov.row, ROLE_ROW, (int)C, dtype, 64, R * batch, &rw.v);
+      int rc = choose(ov.row, ROLE_ROW, (int)C, dtype, 64, R * batch, 0, &rw.v);
       if (rc) return rc;
-      rc = choose(ov.col, ROLE_COL, (int)R, dtype, ov.blk, ov.blk, &cl.v);
+      rc = choose(ov.col, ROLE_COL, (int)R, dtype, ov.blk, ov.blk, 0, &cl.v);
       if (rc) return rc;
       const int64_t T = C / rw.v->P;  // lanes per row (C >= P for every row variant with C >= 8)
       if (rw.v->P > C || T % ov.blk || ov.blk % cl.v->W || R * batch > INT32_MAX) return FFT_ERR_INVALID_ARGUMENT;
@@ -611,7 +680,7 @@ int build_schedule_inner(const int64_t* n, int64_t batch, int dims, int dtype, c
     }
     if (C > 1) {
       PassSpec p;
-      int rc = choose(ov.row, ROLE_ROW, (int)C, dtype, 64, R * batch, &p.v);
+      int rc = choose(ov.row, ROLE_ROW, (int)C, dtype, 64, R * batch, 1, &p.v);
       if (rc) return rc;
       PassArgs& a = p.args;
       a.in_batch = a.out_batch = 0;
@@ -627,7 +696,7 @@ int build_schedule_inner(const int64_t* n, int64_t batch, int dims, int dtype, c
     }
     if (R > 1) {
       PassSpec p;
-      int rc = choose(ov.col, ROLE_COL, (int)R, dtype, 16, C, &p.v);
+      int rc = choose(ov.col, ROLE_COL, (int)R, dtype, 16, C, batch, &p.v);
       if (rc) return rc;
       PassArgs& a = p.args;
       a.in_batch = a.out_batch = R * C;

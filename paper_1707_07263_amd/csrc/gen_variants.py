@@ -136,12 +136,25 @@ def c16_set():
     for lg in range(11, 13):
         if ok(1 << lg, 16, 2):
             out.append(("r", 1 << lg, 16, 2, 0))
+    # rows with 8 points per lane and 256 lanes (512 for short lines, whose
+    # loads then cover more of a line group; whole lines of 4096 and 8192)
+    for lg in range(4, 14):
+        L = 1 << lg
+        for target in (256, 512):
+            W = max(1, target // (L // 8))
+            if W * (L // 8) in (256, 512, 1024):
+                out.append(("r", L, 8, W, 0))
+    out += [("r", 16384, 32, 1, 1)]
     # the split passes of 2^16 and 2^20 with the next tile prefetched (a
     # sixth entry 1: persistent; the prefetch holds 16-bit pairs, one register
     # each) or 128 B row segments (32 pairs per row)
     out += [("a", 1024, 32, 16, 0, 1), ("a", 1024, 32, 16, 0, 2), ("c", 1024, 32, 16, 1, 1),
             ("a", 256, 16, 32, 0, 1), ("c", 256, 16, 32, 0, 1), ("c", 256, 16, 32, 0)]
-    return list(dict.fromkeys(out))
+    # a name once (points per lane are capped at the length)
+    names = {}
+    for v in out:
+        names.setdefault(name(*v[:5], "", *v[5:]), v)
+    return list(names.values())
 
 
 def rowcol_set():
@@ -211,6 +224,9 @@ def pipe_set():
                         if ex and pipe_lds_bytes(L, P, W, 0, role == "a") <= LDS_MAX:
                             continue
                         out.append((role, L, P, W, ex))
+    # lines whose stage twiddles are held as factors (TwFac): 8192 points need
+    # 512 lanes of 16; 16384 points 512 of 32 (one exchange less than 1024 of 16)
+    out += [("r", 8192, 16, 1, 0), ("r", 16384, 32, 1, 0)]
     return out
 
 

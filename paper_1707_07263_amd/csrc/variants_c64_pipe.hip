@@ -28,6 +28,8 @@ void add_variants_c64_pipe(void (*add)(const Variant&)) {
   add(make_variant<ROLE_ROW, 2048, 16, 4, 0, float2, 1>("r2048p16w4q_c64"));
   add(make_variant<ROLE_ROW, 4096, 16, 1, 0, float2, 1>("r4096p16w1q_c64"));
   add(make_variant<ROLE_ROW, 4096, 16, 2, 0, float2, 1>("r4096p16w2q_c64"));
+  add(make_variant<ROLE_ROW, 8192, 16, 1, 0, float2, 1>("r8192p16w1q_c64"));
+  add(make_variant<ROLE_ROW, 16384, 32, 1, 0, float2, 1>("r16384p32w1q_c64"));
   add(make_variant<ROLE_SPLIT_A, 256, 16, 16, 0, float2, 2>("a256p16w16q2_c64"));
   add(make_variant<ROLE_SPLIT_A, 256, 16, 32, 0, float2, 2>("a256p16w32q2_c64"));
   add(make_variant<ROLE_SPLIT_A, 512, 16, 8, 0, float2, 2>("a512p16w8q2_c64"));

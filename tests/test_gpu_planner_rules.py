@@ -1,0 +1,54 @@
+"""Parity of the variants the planner picks by itself, on both sides of the
+tile counts where its choice changes, against the FP64 oracle: rel-L2 <=
+1e-6*log2(N) in complex64, 1e-3 (fp16) and 8e-3 (bf16) on the quantised input."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1707_07263_amd import capi, workloads
+from gpu_helpers import from_gpu_16, quantised, rel_l2_rows, require_gpu, to_gpu_16, to_gpu_c64, tol_fp32
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+DTYPES = {"c64": capi.FFT_C64, "f16": capi.FFT_C16F, "bf16": capi.FFT_C16BF}
+
+
+@pytest.fixture(scope="module")
+def dev():
+    return require_gpu()
+
+
+def check(dev, shape, batch, dt, inverse, schedule=None):
+    n = int(np.prod(shape))
+    x = workloads.normal_batch(n, batch, seed=n % 1009 + batch).reshape([batch] + list(shape))
+    tdt = {"f16": torch.float16, "bf16": torch.bfloat16}.get(dt)
+    xt = to_gpu_c64(x, dev) if dt == "c64" else to_gpu_16(x, dev, tdt)
+    y = torch.empty_like(xt)
+    h = capi.fft_plan_ex(list(shape), batch, len(shape), DTYPES[dt],
+                         capi.FFT_INVERSE if inverse else capi.FFT_FORWARD, schedule)
+    try:
+        capi.fft_exec(h, xt.data_ptr(), y.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    finally:
+        capi.fft_destroy(h)
+    xr = x.astype(np.complex64) if dt == "c64" else quantised(x, tdt)
+    ref = (oracle.fft if len(shape) == 1 else oracle.fft2)(xr, inverse=inverse)
+    got = y.cpu().numpy() if dt == "c64" else from_gpu_16(y)
+    err = rel_l2_rows(got.reshape(batch, n), np.asarray(ref).reshape(batch, n), n).max()
+    assert err <= {"c64": tol_fp32(n), "f16": 1e-3, "bf16": 8e-3}[dt], (shape, batch, dt, inverse, float(err))
+
+
+# one line; a partial tile; for 1024 to 4096 points the last count below the
+# persistent kernel (8 tiles for each of 256 CUs) and the first at it, plus a
+# ragged tile; for the longest lines a persistent walk of more than one round
+ROWS = [(n, b) for n in (2, 8, 16, 32, 64, 256, 512) for b in (1, 37)]
+ROWS += [(1024, 1), (1024, 8188), (1024, 8189), (2048, 3), (2048, 4094), (2048, 4095), (4096, 1), (4096, 2047),
+         (4096, 2048), (8192, 1), (8192, 259), (16384, 1), (16384, 259)]
+
+
+@pytest.mark.parametrize("n,batch", ROWS)
+@pytest.mark.parametrize("dt", sorted(DTYPES))
+def test_rows(dev, n, batch, dt):
+    for inverse in (False, True):
+        check(dev, [n], batch, dt, inverse)
