@@ -119,6 +119,15 @@ size_t esize(int dtype) { return dtype == FFT_C64 ? 8 : 4; }
 // round, 12.5 against 10.4 us for 2^21 points).  Longer rows hold one line per
 // workgroup; their stage twiddles come from factor tables in LDS and the next
 // line is in flight (16384: 82 us against 116).  Short rows take 512 lanes.
+//
+// Columns and first passes of a split: as wide as LDS and registers allow
+// while there are tiles for every CU (two for every CU where a tile of 32
+// lines halves the number), narrower below, since an idle CU costs more than
+// a short row segment (2^20 points in all, 1024-point first pass: 8.4 us with
+// 4 columns per tile against 19 with 16).  First passes are persistent, with
+// the next one or two tiles in flight; second passes alternate two
+// workgroups per CU with the two-round exchange instead (1024 points: 42 us
+// against 59 with 16 points per lane and one workgroup).
 // ---------------------------------------------------------------------------
 struct Pref {
   int role, bits, L;  // bits: storage of one component, 32 or 16
@@ -152,6 +161,75 @@ constexpr Pref kPrefs[] = {
     {ROLE_ROW, 16, 4096, 8, 1, 0, 0, 0},
     {ROLE_ROW, 16, 8192, 8, 1, 0, 0, 0},
     {ROLE_ROW, 16, 16384, 32, 1, 0, 1, 0},
+
+    {ROLE_SPLIT_A, 32, 128, 8, 32, 0, 0, 2 * kCus},
+    {ROLE_SPLIT_A, 32, 128, 8, 16, 0, 0, kCus},
+    {ROLE_SPLIT_A, 32, 128, 8, 8, 0, 0, 0},
+    {ROLE_SPLIT_A, 32, 256, 16, 32, 1, 0, 2 * kCus},
+    {ROLE_SPLIT_A, 32, 256, 16, 16, 1, 0, kCus},
+    {ROLE_SPLIT_A, 32, 256, 8, 4, 0, 0, 0},
+    {ROLE_SPLIT_A, 32, 512, 32, 32, 2, 0, 2 * kCus},
+    {ROLE_SPLIT_A, 32, 512, 32, 16, 2, 0, kCus},
+    {ROLE_SPLIT_A, 32, 512, 16, 8, 2, 0, kCus / 2},
+    {ROLE_SPLIT_A, 32, 512, 8, 4, 0, 0, 0},
+    {ROLE_SPLIT_A, 32, 1024, 32, 16, 2, 0, kCus},
+    {ROLE_SPLIT_A, 32, 1024, 8, 4, 0, 0, 0},
+    {ROLE_SPLIT_A, 32, 2048, 32, 16, 0, 1, 2 * kCus},
+    {ROLE_SPLIT_A, 32, 2048, 16, 8, 0, 0, kCus / 2},
+    {ROLE_SPLIT_A, 32, 2048, 8, 4, 0, 0, 0},
+    {ROLE_SPLIT_A, 16, 128, 16, 64, 1, 0, 2 * kCus},
+    {ROLE_SPLIT_A, 16, 128, 16, 32, 1, 0, 0},
+    {ROLE_SPLIT_A, 16, 256, 16, 32, 1, 0, kCus},
+    {ROLE_SPLIT_A, 16, 256, 16, 16, 1, 0, 0},
+    {ROLE_SPLIT_A, 16, 512, 32, 32, 1, 0, 2 * kCus},
+    {ROLE_SPLIT_A, 16, 512, 8, 16, 1, 0, kCus},
+    {ROLE_SPLIT_A, 16, 512, 8, 8, 1, 0, 0},
+    {ROLE_SPLIT_A, 16, 1024, 32, 16, 1, 0, kCus},
+    {ROLE_SPLIT_A, 16, 1024, 16, 8, 1, 0, 0},
+    {ROLE_SPLIT_A, 16, 2048, 16, 8, 1, 0, kCus},
+    {ROLE_SPLIT_A, 16, 2048, 16, 4, 1, 0, 0},
+    {ROLE_SPLIT_A, 16, 4096, 32, 8, 0, 1, kCus},
+
+    {ROLE_COL, 32, 2, 2, 64, 0, 0, 0},
+    {ROLE_COL, 32, 4, 4, 64, 0, 0, 0},
+    {ROLE_COL, 32, 8, 8, 64, 0, 0, 0},
+    {ROLE_COL, 32, 16, 8, 32, 0, 0, 0},
+    {ROLE_COL, 32, 32, 8, 32, 0, 0, 2 * kCus},
+    {ROLE_COL, 32, 32, 8, 16, 0, 0, 0},
+    {ROLE_COL, 32, 64, 16, 32, 0, 0, 2 * kCus},
+    {ROLE_COL, 32, 64, 8, 16, 0, 0, 0},
+    {ROLE_COL, 32, 128, 16, 16, 0, 0, kCus},
+    {ROLE_COL, 32, 128, 16, 8, 0, 0, 0},
+    {ROLE_COL, 32, 256, 16, 16, 0, 0, kCus},
+    {ROLE_COL, 32, 256, 16, 8, 0, 0, 0},
+    {ROLE_COL, 32, 512, 32, 16, 0, 1, kCus},
+    {ROLE_COL, 32, 512, 8, 8, 0, 0, 0},
+    {ROLE_COL, 32, 1024, 32, 16, 0, 1, kCus},
+    {ROLE_COL, 32, 1024, 16, 8, 0, 0, 0},
+    {ROLE_COL, 32, 2048, 32, 16, 0, 1, 2 * kCus},
+    {ROLE_COL, 32, 2048, 16, 8, 0, 0, kCus},
+    {ROLE_COL, 32, 2048, 16, 4, 0, 0, 0},
+    {ROLE_COL, 32, 4096, 32, 8, 0, 1, kCus},
+    {ROLE_COL, 32, 4096, 16, 4, 0, 0, 0},
+    {ROLE_COL, 16, 2, 2, 64, 0, 0, 0},
+    {ROLE_COL, 16, 4, 4, 64, 0, 0, 0},
+    {ROLE_COL, 16, 8, 8, 64, 0, 0, 0},
+    {ROLE_COL, 16, 16, 16, 64, 0, 0, 0},
+    {ROLE_COL, 16, 32, 16, 64, 0, 0, 0},
+    {ROLE_COL, 16, 64, 16, 64, 0, 0, kCus},
+    {ROLE_COL, 16, 64, 16, 16, 0, 0, 0},
+    {ROLE_COL, 16, 128, 16, 16, 0, 0, 0},
+    {ROLE_COL, 16, 256, 16, 16, 0, 0, kCus},
+    {ROLE_COL, 16, 256, 16, 8, 0, 0, 0},
+    {ROLE_COL, 16, 512, 32, 16, 0, 1, 2 * kCus},
+    {ROLE_COL, 16, 512, 8, 16, 0, 0, kCus},
+    {ROLE_COL, 16, 512, 8, 8, 0, 0, 0},
+    {ROLE_COL, 16, 1024, 32, 16, 0, 1, 2 * kCus},
+    {ROLE_COL, 16, 1024, 32, 8, 0, 0, 0},
+    {ROLE_COL, 16, 2048, 16, 8, 1, 0, 2 * kCus},
+    {ROLE_COL, 16, 2048, 16, 4, 0, 0, 0},
+    {ROLE_COL, 16, 4096, 32, 8, 0, 1, kCus},
+    {ROLE_COL, 16, 4096, 16, 4, 0, 0, 0},
 };
 
 // The preferred variant of a pass over `batches` sets of `lines` lines, or
@@ -211,8 +289,9 @@ struct Schedule {
 struct Overrides {
   int64_t split = 0;
   // per pass, 1: consecutive tiles run on one XCD.  One digit applies to
-  // every pass; otherwise one digit per pass, first pass first.
-  std::string xcd = "0";
+  // every pass; otherwise one digit per pass, first pass first.  Empty: by
+  // the width of the pass's strips (apply_xcd).
+  std::string xcd;
   int col3 = -1;  // 2-D columns in two sub-passes: 1 yes, 0 no, -1 automatic
   int64_t split2 = 0;  // three-pass 1-D: second-pass length
   bool levels = false;  // method=levels: the per-level global-memory method
@@ -303,6 +382,17 @@ int choose(const std::string& name, int role, int L, int dtype, int want_w, int6
 
 constexpr int kSingleMaxLog2 = 14;  // one-kernel transforms up to 2^14 points
 constexpr int kSplitMinLog2 = 6, kSplitMaxLog2 = 12;
+
+// log2 of the first-pass length of a two-pass transform of 2^l points.  For
+// odd l the shorter half goes to the first pass, which costs more per point
+// than the second at the same length (2^21 points, complex64: 1024 x 2048 117
+// us against 127; 2^17: 90.5 against 91.4, bf16 57 against 62), except for
+// 2^15 (a 256-point first pass is persistent, 92 us, a 128-point one is not,
+// 99) and 16-bit storage from 2^19 on (2^21: 82 us against 86).
+int default_split_log2(int l, int dtype) {
+  const bool shorter_first = (l & 1) && l >= 17 && (dtype == FFT_C64 || l == 17);
+  return shorter_first ? l / 2 : (l + 1) / 2;
+}
 
 // 1-D lengths beyond two passes of 2^12: N = N1*N2*N3 in three passes, the
 // four-step identity applied twice.  With n = N2*N3*n1 + N3*n2 + n3 and
@@ -512,7 +602,7 @@ int build_schedule_inner(const int64_t* n, int64_t batch, int dims, int dtype, c
       p.first = p.last = true;
       S.passes.push_back(p);
     } else {
-      int64_t N1 = ov.split ? ov.split : ((int64_t)1 << ((l + 1) / 2));
+      int64_t N1 = ov.split ? ov.split : ((int64_t)1 << default_split_log2(l, dtype));
       if (!pow2(N1) || N1 < 2 || N1 >= N) return FFT_ERR_INVALID_ARGUMENT;
       int64_t N2 = N / N1;
       if (ilog2_64(N1) > kSingleMaxLog2 || ilog2_64(N2) > kSingleMaxLog2) return FFT_ERR_UNSUPPORTED_SIZE;
@@ -722,9 +812,19 @@ int build_schedule_inner(const int64_t* n, int64_t batch, int dims, int dtype, c
   return FFT_OK;
 }
 
-int apply_xcd(const std::string& mask, Schedule* S) {
-  if (S->levels || S->mfma || S->xlane) return mask == "0" || mask == "1" ? FFT_OK : FFT_ERR_INVALID_ARGUMENT;
+int apply_xcd(const std::string& mask, int dtype, Schedule* S) {
+  if (S->levels || S->mfma || S->xlane) return mask.size() <= 1 ? FFT_OK : FFT_ERR_INVALID_ARGUMENT;
   const size_t n = S->passes.size();
+  if (mask.empty()) {
+    // strips whose row segments are narrower than a 128-byte line share each
+    // line with their neighbours: on one XCD the line is fetched into its L2
+    // once (512-point bf16 columns, 16 per tile: 24 us against 34; 4096-point
+    // complex64 columns, 8 per tile: 74 against 85)
+    for (PassSpec& ps : S->passes)
+      ps.args.xcd_remap = ps.v && (ps.v->role == ROLE_SPLIT_A || ps.v->role == ROLE_COL || ps.v->role == ROLE_COL_TW) &&
+                          (size_t)ps.v->W * esize(dtype) < 128;
+    return FFT_OK;
+  }
   if (mask.size() != 1 && mask.size() != n) return FFT_ERR_INVALID_ARGUMENT;
   for (size_t i = 0; i < n; ++i)
     S->passes[i].args.xcd_remap = (mask.size() == 1 ? mask[0] : mask[i]) == '1';
@@ -740,7 +840,7 @@ int build_schedule(const int64_t* n, int64_t batch, int dims, int dtype, const c
   Schedule S;
   int rc = build_schedule_inner(n, batch, dims, dtype, ov, &S);
   if (rc) return rc;
-  rc = apply_xcd(ov.xcd, &S);
+  rc = apply_xcd(ov.xcd, dtype, &S);
   if (rc) return rc;
   *out = S;
   return FFT_OK;

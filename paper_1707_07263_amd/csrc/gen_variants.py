@@ -79,7 +79,8 @@ def strided_set(lo_lg, hi_lg, role):
 
 
 def a_set():
-    return strided_set(6, 12, "a")
+    # and long first passes of 32 points per lane, two-round exchange
+    return strided_set(6, 12, "a") + [(2048, 32, 16, 1), (2048, 32, 8, 1), (4096, 32, 8, 1)]
 
 
 def col_set():
@@ -145,11 +146,22 @@ def c16_set():
             if W * (L // 8) in (256, 512, 1024):
                 out.append(("r", L, 8, W, 0))
     out += [("r", 16384, 32, 1, 1)]
-    # the split passes of 2^16 and 2^20 with the next tile prefetched (a
-    # sixth entry 1: persistent; the prefetch holds 16-bit pairs, one register
-    # each) or 128 B row segments (32 pairs per row)
-    out += [("a", 1024, 32, 16, 0, 1), ("a", 1024, 32, 16, 0, 2), ("c", 1024, 32, 16, 1, 1),
-            ("a", 256, 16, 32, 0, 1), ("c", 256, 16, 32, 0, 1), ("c", 256, 16, 32, 0)]
+    out += [("c", L, 16, 64, 0) for L in (2, 4, 8)]
+    # split and column passes.  A sixth entry: persistent, that many tiles in
+    # flight (held as 16-bit pairs, one register each).  Tiles of 32 pairs
+    # (128 B) per row where the lanes allow it; 16 and fewer under the XCD
+    # remap, which lets neighbouring strips share the lines in one L2
+    out += [("a", 128, 16, 64, 0, 1), ("a", 128, 16, 32, 0, 1),
+            ("a", 256, 16, 32, 0, 1), ("a", 256, 16, 16, 0, 1),
+            ("a", 512, 32, 32, 0, 1), ("a", 512, 8, 16, 0, 1), ("a", 512, 8, 8, 0, 1),
+            ("a", 1024, 32, 16, 0, 1), ("a", 1024, 32, 16, 0, 2), ("a", 1024, 16, 8, 0, 1),
+            ("a", 2048, 16, 8, 0, 1), ("a", 2048, 16, 4, 0, 1),
+            ("a", 4096, 32, 8, 1),
+            ("c", 256, 16, 32, 0, 1), ("c", 256, 16, 32, 0), ("c", 256, 16, 8, 0),
+            ("c", 512, 32, 16, 1), ("c", 512, 8, 16, 0), ("c", 512, 8, 8, 0),
+            ("c", 1024, 32, 16, 1), ("c", 1024, 32, 16, 1, 1), ("c", 1024, 32, 8, 0),
+            ("c", 2048, 16, 8, 0, 1), ("c", 2048, 16, 4, 0),
+            ("c", 4096, 32, 8, 1), ("c", 4096, 16, 4, 0)]
     # a name once (points per lane are capped at the length)
     names = {}
     for v in out:

@@ -76,6 +76,9 @@ void add_variants_c64_a(void (*add)(const Variant&)) {
   add(make_variant<ROLE_SPLIT_A, 2048, 16, 8, 1, float2, 0>("a2048p16w8x_c64"));
   add(make_variant<ROLE_SPLIT_A, 4096, 16, 4, 0, float2, 0>("a4096p16w4_c64"));
   add(make_variant<ROLE_SPLIT_A, 4096, 16, 4, 1, float2, 0>("a4096p16w4x_c64"));
+  add(make_variant<ROLE_SPLIT_A, 2048, 32, 16, 1, float2, 0>("a2048p32w16x_c64"));
+  add(make_variant<ROLE_SPLIT_A, 2048, 32, 8, 1, float2, 0>("a2048p32w8x_c64"));
+  add(make_variant<ROLE_SPLIT_A, 4096, 32, 8, 1, float2, 0>("a4096p32w8x_c64"));
 }
 
 }  // namespace mfft

@@ -52,3 +52,30 @@ ROWS += [(1024, 1), (1024, 8188), (1024, 8189), (2048, 3), (2048, 4094), (2048, 
 def test_rows(dev, n, batch, dt):
     for inverse in (False, True):
         check(dev, [n], batch, dt, inverse)
+
+
+# batches around the tile counts where the passes' widths change: for a
+# first or second pass of 1024 points 16 lines per tile need 256 tiles, for
+# 256 points 32 lines 512; one transform runs the narrowest tiles
+SPLITS = [(1 << 15, 1), (1 << 15, 33), (1 << 16, 1), (1 << 16, 31), (1 << 16, 65), (1 << 17, 1), (1 << 17, 9),
+          (1 << 18, 1), (1 << 18, 3), (1 << 18, 17), (1 << 19, 1), (1 << 19, 5), (1 << 20, 1), (1 << 20, 3),
+          (1 << 20, 5), (1 << 21, 1), (1 << 21, 5), (1 << 22, 1), (1 << 23, 1)]
+
+
+@pytest.mark.parametrize("n,batch", SPLITS)
+@pytest.mark.parametrize("dt", sorted(DTYPES))
+def test_splits(dev, n, batch, dt):
+    check(dev, [n], batch, dt, bool(batch & 2) or n == 1 << 22)
+
+
+# every column length, few and many columns (fewer than the preferred tile is
+# wide among them)
+COLUMNS = [(1 << lg, c, b) for lg in range(1, 12) for c, b in ((4, 3), (64, 2))]
+COLUMNS += [(512, 2048, 1), (1024, 1024, 3), (2048, 512, 3), (32, 4096, 5), (8192, 8, 1), (4096, 8, 2)]
+
+
+@pytest.mark.parametrize("rows,cols,batch", COLUMNS)
+@pytest.mark.parametrize("dt", sorted(DTYPES))
+def test_columns(dev, rows, cols, batch, dt):
+    for inverse in (False, True):
+        check(dev, [rows, cols], batch, dt, inverse)
