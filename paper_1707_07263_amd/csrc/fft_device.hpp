@@ -216,10 +216,11 @@ struct PassArgs {
   const void* in;
   void* out;
   int64_t in_batch, out_batch;  // element stride between batches
-  int64_t in_line, out_line;    // element stride between adjacent lines
-  int64_t in_elem, out_elem;    // element stride between points of a line
+  int64_t in_line, out_line;    // element stride between adjacent lines (1 in strided passes)
+  int64_t in_elem, out_elem;    // element stride between points of a line (1 for contiguous lines)
   int64_t total_tiles;          // tiles_per_batch * batch
   int32_t tiles_per_batch;      // ceil(lines / W)
+  int32_t batch_shift;          // strip passes: tile >> batch_shift is the batch (kOneBatch: one batch)
   int32_t lines;                // lines per batch
   const float2* tw;             // stage table of this (L, P)
   const float2* tw_lo;          // inter-pass: W_N^{j & mask}
@@ -244,19 +245,79 @@ struct PassArgs {
   int32_t blk_lg, blk_rows_lg;
 };
 
+// batch_shift of a launch with one batch: no tile reaches a second one (the
+// other launches have a power of two of tiles per batch).  A shift, since the
+// 64-bit division it stands for is some 100 scalar instructions that every
+// workgroup would run before its first load.
+constexpr int32_t kOneBatch = 40;
+
+// Byte offset of point t of line ln, and between a lane's points.  Strided
+// passes (M = 1) have adjacent lines adjacent in memory, passes over
+// contiguous lines (M = 0) adjacent points.
+template <int M, typename TS>
+__device__ __forceinline__ uint32_t lane_offset(int ln, int t, int64_t line, int64_t elem) {
+  return (M ? (uint32_t)ln + (uint32_t)t * (uint32_t)elem : (uint32_t)ln * (uint32_t)line + (uint32_t)t) * sizeof(TS);
+}
+template <int M, int T, typename TS>
+__device__ __forceinline__ uint32_t point_step(int64_t elem) {
+  return T * (M ? (uint32_t)elem : 1u) * sizeof(TS);
+}
+
 // Where point t + q*T of row `line` goes in the blocked layout: the lane's
 // first element, and the step between its points (T a multiple of the block
 // width, so a lane stays in one column of a block as q runs).
-__device__ __forceinline__ int64_t blk_base(const PassArgs& a, int64_t line, int t) {
-  const int64_t img = line >> a.blk_rows_lg;
-  const int64_t r = line & ((1 << a.blk_rows_lg) - 1);
-  return img * (a.out_line << a.blk_rows_lg) + ((int64_t)(t >> a.blk_lg) << (a.blk_rows_lg + a.blk_lg)) +
-         (r << a.blk_lg) + (t & ((1 << a.blk_lg) - 1));
+// Counted from the image that holds row `line0`, the first of the tile.
+__device__ __forceinline__ uint32_t blk_base(const PassArgs& a, int line0, int line, int t) {
+  const uint32_t img = (uint32_t)(line >> a.blk_rows_lg) - (uint32_t)(line0 >> a.blk_rows_lg);
+  const uint32_t r = (uint32_t)line & ((1u << a.blk_rows_lg) - 1);
+  return img * ((uint32_t)a.out_line << a.blk_rows_lg) + ((uint32_t)(t >> a.blk_lg) << (a.blk_rows_lg + a.blk_lg)) +
+         (r << a.blk_lg) + ((uint32_t)t & ((1u << a.blk_lg) - 1));
 }
 
 __device__ __forceinline__ int row_transpose(int r, int sh) {
   return ((r & ((1 << sh) - 1)) << sh) | (r >> sh);
 }
+
+// The elements a workgroup reads or writes, addressed as a base in scalar
+// registers (a buffer resource), a 32-bit byte offset per lane and a 32-bit
+// byte offset shared by the workgroup: each access then costs at most one
+// scalar addition.  With a pointer per lane the compiler spends a 64-bit
+// vector addition or multiply-add per access (the 512-point bf16 column pass:
+// 691 -> 586 vector instructions per 16 points).  Offsets stay below 2^32: the
+// base is that of a transform or of a tile's first line, and a transform has
+// at most 2^28 points.  Every access moves one element (4 or 8 bytes, dword
+// aligned).
+template <typename TS> struct Strip {
+  static_assert(sizeof(TS) == 4 || sizeof(TS) == 8, "element size");
+  using Raw = typename std::conditional<sizeof(TS) == 8, float2, uint32_t>::type;
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ explicit Strip(const TS* base)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<TS*>(base), 0, 0xffffffffu, 0x00020000)) {}
+  // the element as stored (16-bit pairs packed), STREAM: nontemporal
+  template <bool STREAM = false>
+  __device__ __forceinline__ Raw load_raw(uint32_t lane, uint32_t uni) const {
+    constexpr int aux = STREAM ? 2 : 0;
+    if constexpr (sizeof(TS) == 8)
+      return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, lane, uni, aux));
+    else
+      return __builtin_amdgcn_raw_buffer_load_b32(r, lane, uni, aux);
+  }
+  __device__ __forceinline__ static float2 value(Raw x) {
+    if constexpr (sizeof(TS) == 8) return x;
+    else if constexpr (std::is_same<TS, __half2>::value) return __half22float2(__builtin_bit_cast(__half2, x));
+    else return make_float2(__uint_as_float(x << 16), __uint_as_float(x & 0xffff0000u));
+  }
+  __device__ __forceinline__ void store(uint32_t lane, uint32_t uni, float2 v) const {
+    if constexpr (sizeof(TS) == 8) {
+      typedef uint32_t u2v __attribute__((ext_vector_type(2)));
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2v, v), r, lane, uni, 0);
+    } else if constexpr (std::is_same<TS, __half2>::value) {
+      __builtin_amdgcn_raw_buffer_store_b32(pack_f16x2(v.x, v.y), r, lane, uni, 0);
+    } else {
+      __builtin_amdgcn_raw_buffer_store_b32(pack_bf16x2(v.x, v.y), r, lane, uni, 0);
+    }
+  }
+};
 
 // Map a workgroup id to a tile so that tiles t, t+1, ... run on the same XCD
 // (workgroups are dealt round-robin to the 8 XCDs, each with its own L2).
@@ -505,6 +566,17 @@ __device__ __forceinline__ void run_stages(float2* v, void* lds, int& m, int& t,
 // other lane mappings the persistent pass knows it is absent at compile
 // time, so its loop carries no load whose result the next tile's addresses
 // would wait for.
+// What a strip pass stores for an output: with the inter-pass twiddle
+// (tw_base * tw_row, tw_base already times the pass's scale: a twiddled pass
+// is never the last, so its scale is a power of two and the product exact, and
+// nothing is conjugated), or scaled, the imaginary part by scale_im = -scale
+// for a conjugated result.
+template <bool TWID>
+__device__ __forceinline__ float2 out_value(float2 v, float2 tw_base, float2 tw_row, float scale, float scale_im) {
+  if constexpr (TWID) return cmul(v, cmul(tw_base, tw_row));
+  return make_float2(v.x * scale, v.y * scale_im);
+}
+
 template <int LOADM, int STOREM>
 __host__ __device__ constexpr bool kLineMap() {
   return LOADM == 0 && STOREM == 0;
@@ -532,29 +604,28 @@ k_strip(PassArgs a) {
 
   const int tid = threadIdx.x;
   const int64_t tile = tile_of(blockIdx.x, a.total_tiles, a.xcd_remap);
-  const int64_t bat = tile / a.tiles_per_batch;
-  const int line0 = (int)(tile - bat * a.tiles_per_batch) * W;
+  const int64_t bat = tile >> a.batch_shift;
+  const int tile_in_batch = (int)(tile - (bat << a.batch_shift));
+  const int line0 = tile_in_batch * W;
 
   int m = LOADM ? tid % W : tid / T;
   int t = LOADM ? tid / W : tid % T;
   const int m_st = STOREM ? tid % W : tid / T;
   const int t_st = STOREM ? tid / W : tid % T;
+  const bool lmap = kLineMap<LOADM, STOREM>() && a.line_map;
 
-  const int tile_in_batch = (int)(tile - bat * a.tiles_per_batch);
   float2 v[PP];
   {
     // lines past the end of a partial strip load a valid line and are not stored
-    const int ln = a.line_map ? a.line_map[tile_in_batch * W + m] : min(line0 + m, a.lines - 1);
-    const TS* src = reinterpret_cast<const TS*>(a.in) + bat * a.in_batch +
-                    (int64_t)ln * a.in_line + (int64_t)t * a.in_elem;
-    const int64_t step = (int64_t)T * a.in_elem;
+    const int l0 = lmap ? 0 : line0;
+    const int ln = (lmap ? a.line_map[tile_in_batch * W + m] : min(line0 + m, a.lines - 1)) - l0;
+    const Strip<TS> src(reinterpret_cast<const TS*>(a.in) + bat * a.in_batch + l0 * a.in_line);
+    const uint32_t off = lane_offset<LOADM, TS>(ln, t, a.in_line, a.in_elem);
+    const uint32_t step = point_step<LOADM, T, TS>(a.in_elem);
     const uint32_t sgn = a.conj_in ? 0x80000000u : 0u;
 #pragma unroll
     for (int q = 0; q < PP; ++q) {
-      if constexpr (kStreamLoads<LOADM, W, TS>())
-        v[q] = load_stream(reinterpret_cast<const float2*>(src + q * step));
-      else
-        v[q] = load_c(src + q * step);
+      v[q] = src.value(src.template load_raw<kStreamLoads<LOADM, W, TS>()>(off, q * step));
       v[q].y = __uint_as_float(__float_as_uint(v[q].y) ^ sgn);
     }
   }
@@ -563,16 +634,18 @@ k_strip(PassArgs a) {
 
   // epilogue: inter-pass twiddle, scale, conjugate, store
   {
-    const int line = a.line_map ? row_transpose(a.line_map[tile_in_batch * W + m], a.tr_shift)
-                                : line0 + m;
-    const bool ok = a.line_map ? true : line < a.lines;
-    TS* dst = reinterpret_cast<TS*>(a.out) + bat * a.out_batch + (int64_t)line * a.out_line +
-              (int64_t)t * a.out_elem;
-    int64_t step = (int64_t)T * a.out_elem;
+    const int line = lmap ? row_transpose(a.line_map[tile_in_batch * W + m], a.tr_shift) : line0 + m;
+    const bool ok = lmap || line < a.lines;
+    const int l0 = lmap ? 0 : line0;
+    TS* base = reinterpret_cast<TS*>(a.out) + bat * a.out_batch + l0 * a.out_line;
+    uint32_t off = lane_offset<STOREM, TS>(line - l0, t, a.out_line, a.out_elem);
+    uint32_t step = point_step<STOREM, T, TS>(a.out_elem);
     if (!TWID && STOREM == 0 && a.blk_lg) {
-      dst = reinterpret_cast<TS*>(a.out) + blk_base(a, line, t);
-      step = (int64_t)T << a.blk_rows_lg;
+      base = reinterpret_cast<TS*>(a.out) + (int64_t)(line0 >> a.blk_rows_lg) * (a.out_line << a.blk_rows_lg);
+      off = blk_base(a, line0, line, t) * sizeof(TS);
+      step = (uint32_t)(T * sizeof(TS)) << a.blk_rows_lg;
     }
+    const Strip<TS> dst(base);
     // inter-pass twiddle W_N^{row*(t + q*T)} = W_N^{row*t} * W_N^{row*q*T}
     // (row = line >> tw_line_shift): one base per lane, and a step row
     // shared by the lanes of a line
@@ -582,18 +655,14 @@ k_strip(PassArgs a) {
       const uint32_t row = (uint32_t)line >> a.tw_line_shift;
       const uint32_t jb = row * (uint32_t)t;
       tw_base = cmul(a.tw_hi[jb >> a.tw_shift], a.tw_lo[jb & (uint32_t)a.tw_mask]);
+      tw_base = cscale(tw_base, a.scale);
       tw_row = a.tw_step + (int64_t)row * PP;
     }
-    const uint32_t sgn = a.conj_out ? 0x80000000u : 0u;
+    const float scale_im = a.conj_out ? -a.scale : a.scale;
     if (ok) {
 #pragma unroll
-      for (int q = 0; q < PP; ++q) {
-        float2 y = v[q];
-        if (TWID) y = cmul(y, cmul(tw_base, tw_row[q]));
-        y = cscale(y, a.scale);
-        y.y = __uint_as_float(__float_as_uint(y.y) ^ sgn);
-        store_c(dst + q * step, y);
-      }
+      for (int q = 0; q < PP; ++q)
+        dst.store(off, q * step, out_value<TWID>(v[q], tw_base, TWID ? tw_row[q] : tw_base, a.scale, scale_im));
     }
   }
 }
@@ -653,7 +722,7 @@ k_pipe(PassArgs a) {
   };
   lanes();
   const uint32_t sgn_in = a.conj_in ? 0x80000000u : 0u;
-  const uint32_t sgn_out = a.conj_out ? 0x80000000u : 0u;
+  const float scale_im = a.conj_out ? -a.scale : a.scale;
 
   if constexpr (kPipeTwp<L> == 3)
     TwFac<L, P>::copy(twl, a.tw, tid, NT);
@@ -663,7 +732,7 @@ k_pipe(PassArgs a) {
   // registers of a prefetched tile; 16-bit pairs stay in their storage type
   // (one register each) until they are converted when the tile is consumed.
   // A tile's W*PP step-row entries are held KR per lane.
-  using PreT = typename std::conditional<sizeof(TS) == 8, float2, TS>::type;
+  using PreT = typename Strip<TS>::Raw;
   constexpr int KR = TWID ? (W * PP + NT - 1) / NT : 1;
   struct Pre {
     PreT v[PP];
@@ -671,23 +740,17 @@ k_pipe(PassArgs a) {
     float2 lo, hi;
   };
   auto prefetch = [&](Pre& n, int64_t tl) {
-    const int64_t bat = tl / a.tiles_per_batch;
-    const int line0 = (int)(tl - bat * a.tiles_per_batch) * W;
-    const int tib = (int)(tl - bat * a.tiles_per_batch);
-    const int ln = (kLineMap<LOADM, STOREM>() && a.line_map) ? a.line_map[tib * W + m_ld]
-                                                              : min(line0 + m_ld, a.lines - 1);
-    const TS* src = reinterpret_cast<const TS*>(a.in) + bat * a.in_batch +
-                    (int64_t)ln * a.in_line + (int64_t)t_ld * a.in_elem;
-    const int64_t step = (int64_t)T * a.in_elem;
+    const int64_t bat = tl >> a.batch_shift;
+    const int tib = (int)(tl - (bat << a.batch_shift));
+    const int line0 = tib * W;
+    const bool lmap = kLineMap<LOADM, STOREM>() && a.line_map;
+    const int l0 = lmap ? 0 : line0;
+    const int ln = (lmap ? a.line_map[tib * W + m_ld] : min(line0 + m_ld, a.lines - 1)) - l0;
+    const Strip<TS> src(reinterpret_cast<const TS*>(a.in) + bat * a.in_batch + l0 * a.in_line);
+    const uint32_t off = lane_offset<LOADM, TS>(ln, t_ld, a.in_line, a.in_elem);
+    const uint32_t step = point_step<LOADM, T, TS>(a.in_elem);
 #pragma unroll
-    for (int q = 0; q < PP; ++q) {
-      if constexpr (kStreamLoads<LOADM, W, TS>())
-        n.v[q] = load_stream(reinterpret_cast<const float2*>(src + q * step));
-      else if constexpr (sizeof(TS) == 8)
-        n.v[q] = load_c(src + q * step);
-      else
-        n.v[q] = src[q * step];
-    }
+    for (int q = 0; q < PP; ++q) n.v[q] = src.template load_raw<kStreamLoads<LOADM, W, TS>()>(off, q * step);
     if (TWID) {
       // this tile's step rows W_N^{row*q*T} and the lane's base W_N^{row*t},
       // row = line >> tw_line_shift
@@ -711,10 +774,7 @@ k_pipe(PassArgs a) {
     float2 v[PP];
 #pragma unroll
     for (int q = 0; q < PP; ++q) {
-      if constexpr (sizeof(TS) == 8)
-        v[q] = n.v[q];
-      else
-        v[q] = load_c(&n.v[q]);
+      v[q] = Strip<TS>::value(n.v[q]);
       v[q].y = __uint_as_float(__float_as_uint(v[q].y) ^ sgn_in);
     }
     float2 tw_base = make_float2(1.f, 0.f);
@@ -726,17 +786,17 @@ k_pipe(PassArgs a) {
         // on different banks
         if (W * PP == KR * NT || e < W * PP) rowl[(e / PP) * (PP + 2) + e % PP] = n.row[j];
       }
-      tw_base = cmul(n.hi, n.lo);
+      tw_base = cscale(cmul(n.hi, n.lo), a.scale);
     }
-    const int64_t bat = tile / a.tiles_per_batch;
-    const int line0 = (int)(tile - bat * a.tiles_per_batch) * W;
+    const int64_t bat = tile >> a.batch_shift;
+    const int tib = (int)(tile - (bat << a.batch_shift));
+    const int line0 = tib * W;
     if (ahead < a.total_tiles) prefetch(n, ahead);
 
     int m = m_ld, t = t_ld;
     run_stages<L, P, W, EX, kPipeTwp<L>>(v, xch, m, t, m_st, t_st, LOADM != STOREM, twl);
     if (TWID) lds_barrier();  // step rows visible (also when no exchange ran)
 
-    const int tib = (int)(tile - bat * a.tiles_per_batch);
     const bool lmap = kLineMap<LOADM, STOREM>() && a.line_map;
     const int line = lmap ? row_transpose(a.line_map[tib * W + m], a.tr_shift) : line0 + m;
     // rows past the end of a partial strip loaded a copy of the last line and
@@ -746,21 +806,20 @@ k_pipe(PassArgs a) {
     // the same on every path and the next tile waits for its own prefetch
     // only, not for these stores.
     const int line_st = lmap ? line : min(line, a.lines - 1);
-    TS* dst = reinterpret_cast<TS*>(a.out) + bat * a.out_batch + (int64_t)line_st * a.out_line +
-              (int64_t)t * a.out_elem;
-    int64_t step = (int64_t)T * a.out_elem;
+    const int l0 = lmap ? 0 : line0;
+    TS* base = reinterpret_cast<TS*>(a.out) + bat * a.out_batch + l0 * a.out_line;
+    uint32_t off = lane_offset<STOREM, TS>(line_st - l0, t, a.out_line, a.out_elem);
+    uint32_t step = point_step<STOREM, T, TS>(a.out_elem);
     if (!TWID && STOREM == 0 && a.blk_lg) {
-      dst = reinterpret_cast<TS*>(a.out) + blk_base(a, line_st, t);
-      step = (int64_t)T << a.blk_rows_lg;
+      base = reinterpret_cast<TS*>(a.out) + (int64_t)(line0 >> a.blk_rows_lg) * (a.out_line << a.blk_rows_lg);
+      off = blk_base(a, line0, line_st, t) * sizeof(TS);
+      step = (uint32_t)(T * sizeof(TS)) << a.blk_rows_lg;
     }
+    const Strip<TS> dst(base);
 #pragma unroll
-    for (int q = 0; q < PP; ++q) {
-      float2 y = v[q];
-      if (TWID) y = cmul(y, cmul(tw_base, rowl[m * (PP + 2) + q]));
-      y = cscale(y, a.scale);
-      y.y = __uint_as_float(__float_as_uint(y.y) ^ sgn_out);
-      store_c(dst + q * step, y);
-    }
+    for (int q = 0; q < PP; ++q)
+      dst.store(off, q * step,
+                out_value<TWID>(v[q], tw_base, TWID ? rowl[m * (PP + 2) + q] : tw_base, a.scale, scale_im));
     lds_barrier();  // LDS reads of this tile done before the next one overwrites
   };
 

@@ -190,6 +190,11 @@ constexpr Pref kPrefs[] = {
     {ROLE_SPLIT_A, 16, 2048, 16, 4, 1, 0, 0},
     {ROLE_SPLIT_A, 16, 4096, 32, 8, 0, 1, kCus},
 
+    // twiddled columns of the three-pass plan: 64 columns while the
+    // intermediate fits the 256 MB last-level cache (2^25 points 100 us against
+    // 108), 32 beyond (2^26 207 against 211); other lengths as pick() has it
+    {ROLE_COL_TW, 32, 128, 16, 32, 0, 0, 64 * kCus},
+
     {ROLE_COL, 32, 2, 2, 64, 0, 0, 0},
     {ROLE_COL, 32, 4, 4, 64, 0, 0, 0},
     {ROLE_COL, 32, 8, 8, 64, 0, 0, 0},
@@ -1262,6 +1267,10 @@ int fft_plan_ex(const int64_t* n, int64_t batch, int dims, int dtype, int direct
   for (size_t i = 0; i < p->sched.passes.size(); ++i) {
     PassSpec& ps = p->sched.passes[i];
     if (!ps.v) continue;
+    // tiles per batch are a power of two wherever there are several batches
+    // (lines and tile widths are); rows of one batch may be any number
+    ps.args.batch_shift =
+        ps.args.total_tiles > ps.args.tiles_per_batch ? ilog2_64(ps.args.tiles_per_batch) : kOneBatch;
     if (ps.v->persistent) {
       // persistent variants launch the resident workgroups only
       const int per_cu = std::max(1, ps.v->blocks_per_cu());
