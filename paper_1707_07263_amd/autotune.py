@@ -34,6 +34,7 @@ CACHE_PATH = os.environ.get("MI355FFT_TUNE_CACHE", os.path.join(HERE, "tuned_sch
 ARCH = "gfx950"
 _lock = threading.Lock()
 _cache = None
+generation = 0  # raised whenever the schedules change in this process
 
 ROLE_ROW, ROLE_A, ROLE_COL, ROLE_COL_TW, ROLE_ROWCOL = 0, 1, 2, 3, 4
 
@@ -81,8 +82,9 @@ def save(entries: dict, path: str | None = None) -> None:
         with open(tmp, "w") as f:
             json.dump(c, f, indent=1, sort_keys=True)
         os.replace(tmp, path)
-        global _cache
+        global _cache, generation
         _cache = c
+        generation += 1
 
 
 # ---------------------------------------------------------------------------
