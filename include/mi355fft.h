@@ -152,22 +152,25 @@ int fft_plan_ex(const int64_t *n, int64_t batch, int dims, int dtype, int direct
  * Plan `count` independent 1-D transforms whose lengths sizes[0..count) are
  * powers of two in 1 .. 2^24, packed back to back in the given order (the
  * offset of transform i is the sum of sizes[0..i)).  fft_exec runs them all
- * with one persistent kernel.  By default ('pipe=2' below) it is launched
- * twice per exec: the first launch runs every one-pass transform and the
- * first pass of every two-pass one, the second launch every second pass, so
- * the kernel boundary orders each transform's passes (Sec. 2.3.3); inside a
- * launch the workgroups claim work items from a device queue and never wait
- * for one another.  The single-launch kernels ('pipe=0|1') chain a
- * transform's passes by a completion counter instead.  The queue state lives
- * in the plan's workspace and is reset by the kernel itself, so the launches
- * can be captured in a hipGraph and replayed.  Two fft_exec calls that share one workspace must not run
+ * in two launches: the first runs every one-pass transform and the first pass
+ * of every two-pass one, the second (skipped if there is none) every second
+ * pass, so the kernel boundary orders each transform's passes (Sec. 2.3.3).
+ * By default every tile is a workgroup of its own.  The persistent kernels of
+ * the schedule string below claim their tiles from a device queue: 'pipe=2' in
+ * the same two launches, 'pipe=0|1' in one, chaining a transform's passes by a
+ * completion counter.  Their queue state lives in the plan's workspace and is
+ * reset by the kernel itself, so the launches can be captured in a hipGraph
+ * and replayed.  Two fft_exec calls that share one workspace must not run
  * concurrently.
  */
 int fft_plan_many(const int64_t *sizes, int64_t count, int dtype, int direction,
                   fft_plan_t *out);
 
 /*
- * As fft_plan_many with a schedule string of ';'-separated items:
+ * As fft_plan_many with a schedule string of ';'-separated items.  A string
+ * with none of p, threads, pipe, lag, ntst and ntail plans the default kernel,
+ * one workgroup of 512 lanes with 8 points each per tile.
+ *   'flat=1'           that kernel by name (with none of the six)
  *   'p=' 8|16          points per lane (radix of the in-register stages)
  *   'threads=' 256|512 workgroup size (not every dtype has every size;
  *                      default 512)
@@ -182,13 +185,13 @@ int fft_plan_many(const int64_t *sizes, int64_t count, int dtype, int direction,
  *                      queue order, completion counters as in 0 -- its
  *                      progress needs every workgroup of the launch resident
  *                      at once, so it is only for a GPU the launch has to
- *                      itself; 2 (the default): the same pipelining in two
+ *                      itself; 2 (when one of the six items is given): the same pipelining in two
  *                      launches per exec (first passes and one-pass tiles,
  *                      then second passes; the kernel boundary orders a
  *                      transform's passes and no workgroup waits for another),
  *                      items claimed from each launch's atomic queue head.
- *                      fft_plan_info names the kernel many_queue, many_pipe
- *                      or many_2launch
+ *                      fft_plan_info names the kernel many_flat (default),
+ *                      many_queue, many_pipe or many_2launch
  *   'pass.L=' 1|2      length 2^L in one pass or two (one needs 2^L within
  *                      the longest tile)
  *   'n1.L=' l          two passes for length 2^L with a first pass of 2^l

@@ -26,8 +26,9 @@ class Plan:
         self.kind = kind
         self.workspace = None  # torch tensor backing a caller-owned workspace
         # batched plans whose kernel waits on completion counters (the
-        # two-launch kernel never waits)
-        self.waits = kind == "many" and capi.fft_plan_info(handle)["pass_variant"][0] != "many_2launch"
+        # two-launch kernels never wait)
+        self.waits = kind == "many" and capi.fft_plan_info(handle)["pass_variant"][0] not in ("many_flat",
+                                                                                               "many_2launch")
 
     def __del__(self):
         try:
@@ -195,7 +196,7 @@ def ifft2(x: torch.Tensor, **kw) -> torch.Tensor:
 def fft_many(packed: torch.Tensor, sizes, inverse: bool = False, *, scale=None,
              out: torch.Tensor | None = None, schedule: str | None = None) -> torch.Tensor:
     """Independent 1-D transforms of lengths `sizes` packed back to back, in
-    one persistent launch."""
+    one exec (two launches)."""
     inverse = bool(inverse)
     key = None
     if type(sizes) in (list, tuple):

@@ -311,7 +311,10 @@ def tune_many(sizes, dtype=capi.FFT_C64, reps=10, verbose=False):
                     for order in ("bigfirst", "given"):
                         grid.append(f"p={P};threads={threads};pass2={pass2};order={order}"
                                     + (";pipe=1" if pipe else ";pipe=0"))
-    # the two-launch kernel (512 lanes, tiles up to 2^12)
+    # the plain-grid kernel, and the two-launch persistent one (512 lanes,
+    # tiles up to 2^12)
+    for pass2 in range(9, 14):
+        grid.append(f"flat=1;pass2={pass2}")
     for pass2 in range(9, 14):
         grid.append(f"p=16;threads=512;pipe=2;pass2={pass2}")
     best = None
@@ -319,7 +322,7 @@ def tune_many(sizes, dtype=capi.FFT_C64, reps=10, verbose=False):
         us = timed(s)
         if us is not None and (best is None or us < best[0]):
             best = (us, s)
-    if best is not None and "pipe=2" not in best[1]:
+    if best is not None and "pipe=2" not in best[1] and "flat=1" not in best[1]:
         # queue order: second passes lagging the first passes by k transforms
         base = best[1]
         for lag in (1, 2, 4, 8):
@@ -349,7 +352,7 @@ def _tune_per_length(sizes, best, timed):
         return int(m.group(1)) if m else default
     threads, P, pipe = opt("threads", 256), opt("p", 16), opt("pipe", 0)
     base = best[1]
-    max_tile = min(12 if (pipe != 1 or threads == 512) else 11, int(math.log2(threads * P)))
+    max_tile = 12 if "flat=1" in base else min(12 if (pipe != 1 or threads == 512) else 11, int(math.log2(threads * P)))
     pass2 = opt("pass2", max_tile + 1)
     cur = dict()
     for _ in range(2):

@@ -146,8 +146,11 @@ template <int L, int P> struct Sched {
 // stepping 32 points inside a line fall on different banks (measured against
 // one pad per 16 points with an odd stride: the 2-D image 142.3 -> 137.1 us,
 // the other workloads unchanged or slightly faster).
+// Lines of fewer than 16 points, which only the batched kernels exchange,
+// take one slot more than their length, so that no length needs more LDS
+// than 16 does.
 template <int L> struct LdsLayout {
-  static constexpr int LS = L + (L >> 5) + 2;
+  static constexpr int LS = L + (L >> 5) + (L < 16 ? 1 : 2);
   __device__ __forceinline__ static int idx(int m, int e) { return m * LS + e + (e >> 5); }
 };
 

@@ -1051,9 +1051,12 @@ struct ManyOptions {
   int P = 16, threads = 512, pass2 = 0;  // pass2 0: two passes above the longest one-tile length
   bool given_order = false;
   // 0: shared queue with completion counters; 1: software-pipelined, one
-  // workgroup per CU, round-robin items, completion counters; 2 (default):
-  // software-pipelined, two launches per exec, no waits
+  // workgroup per CU, round-robin items, completion counters; 2:
+  // software-pipelined, two launches per exec, no waits; 3: plain grid, two
+  // launches (the default when the schedule names no kernel)
   int pipe = 2;
+  bool flat = false;          // the plain-grid kernel asked for by name
+  bool kernel_named = false;  // an option of the other kernels was given
   // 0: every first-pass tile ahead of every second-pass tile; k > 0: the
   // second-pass tiles of split transform i follow the first-pass tiles of
   // split transform i + k, so its intermediate is still in the last-level
@@ -1072,8 +1075,7 @@ struct ManyOptions {
 };
 
 int parse_many_schedule(const char* s, ManyOptions* o) {
-  if (!s) return FFT_OK;
-  std::string str(s);
+  std::string str(s ? s : "");
   size_t pos = 0;
   while (pos < str.size()) {
     size_t end = str.find(';', pos);
@@ -1111,6 +1113,12 @@ int parse_many_schedule(const char* s, ManyOptions* o) {
       }
       continue;
     }
+    if (key == "flat") {
+      if (v != 1) return FFT_ERR_INVALID_ARGUMENT;
+      o->flat = true;
+      continue;
+    }
+    o->kernel_named |= key != "pass2";
     if (key == "p") o->P = (int)v;
     else if (key == "threads") o->threads = (int)v;
     else if (key == "pass2") {
@@ -1131,6 +1139,12 @@ int parse_many_schedule(const char* s, ManyOptions* o) {
       o->lag = (int)v;
     }
     else return FFT_ERR_INVALID_ARGUMENT;
+  }
+  if (o->flat && o->kernel_named) return FFT_ERR_INVALID_ARGUMENT;
+  if (!o->kernel_named) {
+    o->pipe = 3;
+    o->P = 8;
+    o->threads = (1 << kManyMaxLg) / o->P;
   }
   return FFT_OK;
 }
@@ -1384,7 +1398,7 @@ int exec_impl(fft_plan_t p, const void* in, void* out, void* stream, void* ws_ov
     const char* mo = (const char*)out;
     if (in != out && mi < mo + mbytes && mo < mi + mbytes) return FFT_ERR_INPLACE;
     if (p->many.has_split && in == out) return FFT_ERR_INPLACE;
-    if (ws_over) {
+    if (ws_over && p->many.var->pipe != 3) {
       const int64_t words = (int64_t)(many_workspace_bytes(p->many) / sizeof(uint32_t));
       hipLaunchKernelGGL(k_zero_words, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 1024)), dim3(256),
                          0, s, (uint32_t*)ws_over, words);
@@ -1567,11 +1581,11 @@ int fft_plan_info(fft_plan_t p, fft_plan_info_t* info) {
   const double es = (double)esize(p->dtype);
   if (p->kind == 1) {
     info->passes = 1;
-    // the batched kernel: many_2launch (two launches, no waits), many_queue
+    // the batched kernel: many_flat and many_2launch (two launches, no waits), many_queue
     // (shared queue, completion counters), many_pipe (round-robin items,
     // completion counters)
     const int pipe = p->many.var ? p->many.var->pipe : 0;
-    snprintf(info->pass_variant[0], 32, "%s", pipe == 2 ? "many_2launch" : pipe == 1 ? "many_pipe" : "many_queue");
+    snprintf(info->pass_variant[0], 32, "%s", pipe == 3 ? "many_flat" : pipe == 2 ? "many_2launch" : pipe == 1 ? "many_pipe" : "many_queue");
     info->points = p->many.points;
     info->flops = p->many.flops;
     info->bytes_min = 2.0 * es * (double)p->many.points;
@@ -1893,7 +1907,7 @@ int build_many(const int64_t* sizes, int64_t count, int dtype, int direction, co
   }
   while (b_next < split_ids.size()) push_b(split_ids[b_next++]);
   if (items.size() > (size_t)INT32_MAX / 2) return FFT_ERR_UNSUPPORTED_SIZE;
-  if (opt.pipe == 2) split_launches(mb);
+  if (opt.pipe >= 2) split_launches(mb);
   return FFT_OK;
 }
 
@@ -2031,7 +2045,7 @@ int fft_plan_many_ex(const int64_t* sizes, int64_t count, int dtype, int directi
     return FFT_OK;
   };
   rc = upload((void**)&mp.d_items, items.data(), items.size() * sizeof(ManyItem));
-  if (!rc && opt.pipe == 2) {
+  if (!rc && opt.pipe >= 2) {
     // one self-contained record per item, grouped by queue
     std::vector<ManyItemX> itx(items.size());
     size_t launch = 0;
@@ -2088,7 +2102,7 @@ int fft_plan_many_ex(const int64_t* sizes, int64_t count, int dtype, int directi
   a.tw_used = 0;
   for (int lg = 1; lg <= max_tile; ++lg)
     if (used[lg]) a.tw_used |= 1 << lg;
-  if (var->pipe) {
+  if (var->pipe == 1 || var->pipe == 2) {
     // the pipelined kernel's LDS image of the stage twiddles, gathered once
     std::vector<int32_t> map;
     const int len = many_tw_image_map(a.stage_off, a.tw_used, opt.P, var->max_lg, &map);
@@ -2130,7 +2144,8 @@ int fft_plan_many_ex(const int64_t* sizes, int64_t count, int dtype, int directi
   a.itx = mp.d_itx;
   a.q_off = mp.d_q_off;
   a.phase = 0;
-  a.n_phase2 = opt.pipe == 2 ? mb.q_off[2] - mb.q_off[1] : 0;
+  a.n_phase1 = opt.pipe >= 2 ? mb.q_off[1] : 0;
+  a.n_phase2 = opt.pipe >= 2 ? mb.q_off[2] - mb.q_off[1] : 0;
   int cus = 0;
   e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device);
   if (e != hipSuccess) {

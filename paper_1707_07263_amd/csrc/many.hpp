@@ -78,10 +78,10 @@ struct ManyArgs {
   int32_t tw_img_len;
   // two-launch kernel: items in launch order, launch p running items
   // q_off[p] .. q_off[p+1]-1 (p = phase: 0 first passes and one-pass tiles,
-  // 1 second passes); n_phase2 = q_off[2] - q_off[1]
+  // 1 second passes); n_phase1 and n_phase2 items
   const ManyItemX* itx;
   const int32_t* q_off;
-  int32_t phase, n_phase2;
+  int32_t phase, n_phase1, n_phase2;
   int32_t tw_img_len_ph[2];  // two-launch kernel: image entries each launch's lengths need
   int32_t* watchdog;  // flag set when a bounded wait expires
 };
@@ -94,7 +94,8 @@ constexpr int kManyWsHeader = 4;  // ints before the per-transform counters
 
 struct ManyVariant {
   int dtype, P, threads;
-  int pipe;    // 1: software-pipelined; 2: software-pipelined, two launches per exec
+  int pipe;    // 1: software-pipelined; 2: software-pipelined, two launches per exec;
+               // 3: plain grid, one workgroup per item, two launches per exec
   int max_lg;  // longest one-tile length, 2^max_lg
   hipError_t (*launch)(const ManyArgs&, int grid, hipStream_t);
   int (*max_blocks_per_cu)();

@@ -79,3 +79,38 @@ COLUMNS += [(512, 2048, 1), (1024, 1024, 3), (2048, 512, 3), (32, 4096, 5), (819
 def test_columns(dev, rows, cols, batch, dt):
     for inverse in (False, True):
         check(dev, [rows, cols], batch, dt, inverse)
+
+
+# lengths whose tiles are partly filled: fewer lines than a tile of 4096
+# points holds, fewer columns than a strip is wide, second passes shorter and
+# longer than the first, an item count on either side of the pairing by 16,
+# every first-pass length down to 2 points
+MANY = [[1], [2] * 5, [4096], [8192], [1 << 15], [1 << k for k in range(17)], [64] * 1025, [1 << 13] * 9,
+        [1 << 16] * 3 + [8] * 7 + [1 << 12] * 2, [1 << 20, 1 << 14], [256, 1 << 17, 16]]
+
+
+@pytest.mark.parametrize("sizes", MANY, ids=lambda s: f"{len(s)}x{max(s)}")
+@pytest.mark.parametrize("schedule", [None, "flat=1;pass2=2", "flat=1;n1.13=1;n1.14=3;n1.16=12;n1.15=3"])
+@pytest.mark.parametrize("dt", sorted(DTYPES))
+def test_many_default_kernel(dev, sizes, schedule, dt):
+    total = sum(sizes)
+    x = workloads.normal_batch(total, 1, seed=total % 997)[0]
+    tdt = {"f16": torch.float16, "bf16": torch.bfloat16}.get(dt)
+    xt = to_gpu_c64(x, dev) if dt == "c64" else to_gpu_16(x, dev, tdt)
+    xr = x.astype(np.complex64) if dt == "c64" else quantised(x, tdt)
+    for inverse in (False, True):
+        h = capi.fft_plan_many_ex(sizes, DTYPES[dt], capi.FFT_INVERSE if inverse else capi.FFT_FORWARD, schedule)
+        try:
+            assert capi.fft_plan_info(h)["pass_variant"] == ["many_flat"]
+            y = torch.empty_like(xt)
+            capi.fft_exec(h, xt.data_ptr(), y.data_ptr(), torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+        finally:
+            capi.fft_destroy(h)
+        got = y.cpu().numpy() if dt == "c64" else from_gpu_16(y)
+        ref = oracle.fft_many(xr, np.array(sizes), inverse=inverse)
+        at = 0
+        for n in sizes:
+            err = rel_l2_rows(got[at:at + n], ref[at:at + n], n).max()
+            assert err <= {"c64": tol_fp32(n), "f16": 1e-3, "bf16": 8e-3}[dt], (n, inverse, float(err))
+            at += n
