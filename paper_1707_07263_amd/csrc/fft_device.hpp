@@ -474,16 +474,43 @@ __device__ __forceinline__ void exchange(float2* v, void* ldsv, int m, int m2, i
 // Stages are unrolled by compile-time recursion so that every radix, span
 // and register index is a constant.
 // ---------------------------------------------------------------------------
+// Factors of stage s read from the global table (TWP 0), loaded one stage
+// ahead: before the previous stage's butterflies and exchange, which hide the
+// L2 latency that a load at the point of use would add to every stage.  Up to
+// 16 points per lane; with 32 they would not fit beside the points in the 128
+// registers that two workgroups per CU allow.
+template <int L, int P, int s, int TWP> struct StageTw {
+  using S = Sched<L, P>;
+  static constexpr bool AHEAD = TWP == 0 && s > 0 && s < S::S && S::PP <= 16;
+  static constexpr int N = AHEAD ? S::PP : 1;
+  float2 w[N];
+  // for the lane that holds points t + q*T in stage s
+  __device__ __forceinline__ void load(const float2* __restrict__ twt, int t) {
+    if constexpr (AHEAD) {
+      constexpr int R = S::radix(s), NS = S::ns(s), NB = S::PP / R;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const float2* tw = twt + S::off(s) + ((t + b * S::T) & (NS - 1)) * R;
+#pragma unroll
+        for (int r = 1; r < R; ++r) w[b * R + r] = tw[r];
+      }
+    }
+  }
+};
+
 template <int L, int P, int EX, int s, int TWP = 0>
 struct Stage {
   using S = Sched<L, P>;
+  using TW = StageTw<L, P, s, TWP>;
   static constexpr int T = S::T;
   static constexpr int PP = S::PP;
   static constexpr int R = S::radix(s);
   static constexpr int NS = S::ns(s);
   static constexpr int NB = PP / R;
   __device__ __forceinline__ static void run(float2* v, void* lds, int& m, int& t, int m_st,
-                                             int t_st, const float2* __restrict__ twt) {
+                                             int t_st, const float2* __restrict__ twt, const TW& ahead) {
+    StageTw<L, P, s + 1, TWP> next;
+    if constexpr (s + 1 < S::S) next.load(twt, t_st);
     int o0[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -493,7 +520,10 @@ struct Stage {
       float2 x[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) x[r] = v[b + r * NB];
-      if constexpr (s > 0 && TWP == 2) {
+      if constexpr (TW::AHEAD) {
+#pragma unroll
+        for (int r = 1; r < R; ++r) x[r] = cmul(x[r], ahead.w[b * R + r]);
+      } else if constexpr (s > 0 && TWP == 2) {
         // TWP 2: W_{NS*R}^{k r} = W_L^e, e = k r L/(NS R), from two factor
         // tables in LDS, twt[i] = W_L^i (i < 2^LA) and
         // twt[2^LA + i] = W_L^{i 2^LA}: a few hundred bytes instead of the
@@ -527,7 +557,7 @@ struct Stage {
       exchange<L, PP, EX, R, NS>(v, lds, m, m_st, t_st, o0);
       m = m_st;
       t = t_st;
-      Stage<L, P, EX, s + 1, TWP>::run(v, lds, m, t, m_st, t_st, twt);
+      Stage<L, P, EX, s + 1, TWP>::run(v, lds, m, t, m_st, t_st, twt, next);
     }
   }
 };
@@ -539,7 +569,7 @@ __device__ __forceinline__ void run_stages(float2* v, void* lds, int& m, int& t,
   using S = Sched<L, P>;
   constexpr int T = S::T;
   constexpr int PP = S::PP;
-  Stage<L, P, EX, 0, TWP>::run(v, lds, m, t, m_st, t_st, twt);
+  Stage<L, P, EX, 0, TWP>::run(v, lds, m, t, m_st, t_st, twt, StageTw<L, P, 0, TWP>());
   if constexpr (S::S == 1) {
     if (remap) {
       // one-stage transform whose load and store mappings differ: transpose
