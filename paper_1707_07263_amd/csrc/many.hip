@@ -120,6 +120,16 @@ __device__ __forceinline__ void many_tile(const ManyArgs& a, const ManyItem& d, 
   }
 }
 
+// Every wave of a workgroup, before the barrier that precedes thread 0's
+// device-scope release of a first-pass tile: its stores have reached L2.  The
+// barrier itself does not wait for them (workgroup scope: one CU, one L1), and
+// the release writes back what is in L2 at that moment, so a store still on
+// its way would be missing for a second-pass tile on another XCD.
+__device__ __forceinline__ void stores_done() {
+  asm volatile("" ::: "memory");
+  vm_wait<0>();
+}
+
 // Length-1 lines: NT transforms of one point each.
 template <int NT, typename TS>
 __device__ __forceinline__ void many_tile1(const ManyArgs& a, const ManyItem& d, int tid) {
@@ -187,8 +197,9 @@ __global__ void __launch_bounds__(NT) k_many(ManyArgs a) {
       case 12: if constexpr (NT * P >= 4096) many_tile<4096, P, NT, TS>(a, d, lds, tid); break;
       default: break;
     }
-    // the barrier orders every wave's stores of this tile before thread 0's
-    // agent-scope release, which makes them visible to the other XCDs
+    // every wave's stores of this tile come before thread 0's agent-scope
+    // release, which makes them visible to the other XCDs
+    if (d.kind == MANY_A) stores_done();
     __syncthreads();
     if (d.kind == MANY_A && tid == 0)
       __hip_atomic_fetch_add(&done[d.a], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -561,6 +572,7 @@ __global__ void __launch_bounds__(NT, 1) k_many_pipe(ManyArgs a) {
       // every lane)
       const bool look = has_next && nxt2 < a.n_items && dn2.kind == MANY_B;
       if (pending < 0 && !look) return;
+      if (pending >= 0) stores_done();
       __syncthreads();
       if (tid == 0) {
         if (pending >= 0)
@@ -609,6 +621,7 @@ __global__ void __launch_bounds__(NT, 1) k_many_pipe(ManyArgs a) {
     if (has_next && !ready) {
       // its first pass was still running at the check: release ours (it may
       // be one of them), wait, then load
+      if (pending >= 0) stores_done();
       __syncthreads();
       if (tid == 0) {
         if (pending >= 0)
@@ -627,6 +640,7 @@ __global__ void __launch_bounds__(NT, 1) k_many_pipe(ManyArgs a) {
     ready = ready2;
   }
   if (pending >= 0) {
+    stores_done();
     __syncthreads();
     if (tid == 0) __hip_atomic_fetch_add(&done[pending], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
   }
