@@ -25,6 +25,7 @@ class Plan:
         self.handle = handle
         self.kind = kind
         self.workspace = None  # torch tensor backing a caller-owned workspace
+        self.own_workspace = False  # an in-place exec brings its workspace
         # batched plans whose kernel waits on completion counters (the
         # two-launch kernels never wait)
         self.waits = kind == "many" and capi.fft_plan_info(handle)["pass_variant"][0] not in ("many_flat",
@@ -42,6 +43,8 @@ class Plan:
     def exec(self, x: torch.Tensor, out: torch.Tensor, stream: int | None = None) -> None:
         if stream is None:
             stream = _raw_stream(x.device.index)
+        if self.own_workspace and x.data_ptr() == out.data_ptr():
+            self.ensure_workspace(x.device)
         capi.fft_exec(self.handle, x.data_ptr(), out.data_ptr(), stream)
 
     def set_scale(self, s: float) -> None:
@@ -85,8 +88,11 @@ def get_plan(shape, batch: int, dtype: int, direction: int, *, scale=None,
              schedule: str | None = None, device=None) -> Plan:
     """Cached plan for `batch` transforms of `shape` (1 or 2 dims)."""
     dev = torch.cuda.current_device() if device is None else torch.device(device).index
+    # 2-D plans need no workspace in place unless the rule's passes do
+    own_workspace = False
     if schedule is None:
         schedule = autotune.schedule_for(shape, batch, dtype)
+        own_workspace = schedule is not None and schedule == autotune.rule_for(shape, dtype)
     key = ("plan", tuple(int(s) for s in shape), int(batch), dtype, direction, scale, schedule, dev)
     with _lock:
         p = _cache.get(key)
@@ -97,6 +103,7 @@ def get_plan(shape, batch: int, dtype: int, direction: int, *, scale=None,
                 if scale is not None:
                     p.set_scale(scale)
             _cache[key] = p
+        p.own_workspace |= own_workspace
     return p
 
 

@@ -60,11 +60,44 @@ def _many_key(sizes, dtype):
     return f"{ARCH}|many|{len(sizes)}|{h}|{int(dtype)}"
 
 
+# 2-D plans of 2048 rows or more.  A column tile of 2048 or 4096 points holds 16
+# or 8 columns and one workgroup per CU, and runs 58 to 100 us over 2^24
+# complex64 points; with the first radix-r step of the columns in the row pass
+# (rowcol=r) the rest are columns of R/r points, 41 to 45 us (and 60 for
+# 8192 rows), and the row pass takes 0 to 8 us more.  Per row length the fused
+# variants for r = 2 and 4.  Both passes together, 2^24 points: 2048 x 1024
+# 106 -> 93 us, 2048 x 4096 109 -> 96, 4096 x 512 144 -> 98, 4096 x 2048 142 -> 96,
+# 8192 x 1024 180 -> 109; 2^22 points: 31 -> 30, 35 -> 30, 45 -> 31.  r = 2 leaves
+# the row pass of long rows two workgroups per CU, but 2048-point columns of a
+# 4096-row image cost more than that gains (108 against 96).
+_FUSED_ROWS = {256: {4: "f256p8w4q_c64"}, 512: {4: "f512p8w4q_c64"}, 1024: {4: "f1024p16w4q_c64"},
+               2048: {2: "f2048p16w2q_c64", 4: "f2048p16w4q_c64"},
+               4096: {2: "f4096p16w2q_c64", 4: "f4096p16w4qx_c64"}}
+
+
+def rule_for(shape, dtype):
+    """Schedule string by the shape alone where the planner's own choice of
+    passes is not the fastest, or None."""
+    if len(shape) != 2:
+        return None
+    rows, cols = int(shape[0]), int(shape[1])
+    fused = _FUSED_ROWS.get(cols) if dtype == capi.FFT_C64 else None
+    if fused and rows in (2048, 4096, 8192, 16384):
+        r = 2 if rows == 2048 and 2 in fused else 4
+        return f"rowcol={r};row={fused[r]}"
+    if rows == 4096 and cols > 1:
+        # rows, then whole columns: 2^24 points in 16-bit storage 77-91 us
+        # against 88-106 in three passes, complex64 with 32 or 128 columns
+        # 127-129 against 138-141
+        return "col3=0"
+    return None
+
+
 def schedule_for(shape, batch, dtype):
-    """Tuned schedule string for a strided plan, or None."""
+    """Tuned schedule string for a strided plan, or the rule's, or None."""
     with _lock:
         e = _load_cache().get(_key("plan", shape, batch, dtype))
-    return None if e is None else e["schedule"]
+    return rule_for(shape, dtype) if e is None else e["schedule"]
 
 
 def many_schedule_for(sizes, dtype):

@@ -252,7 +252,7 @@ struct PassArgs {
 // other launches have a power of two of tiles per batch).  A shift, since the
 // 64-bit division it stands for is some 100 scalar instructions that every
 // workgroup would run before its first load.
-constexpr int32_t kOneBatch = 40;
+constexpr int32_t kOneBatch = 31;
 
 // Byte offset of point t of line ln, and between a lane's points.  Strided
 // passes (M = 1) have adjacent lines adjacent in memory, passes over
@@ -324,7 +324,8 @@ template <typename TS> struct Strip {
 
 // Map a workgroup id to a tile so that tiles t, t+1, ... run on the same XCD
 // (workgroups are dealt round-robin to the 8 XCDs, each with its own L2).
-__device__ __forceinline__ int64_t tile_of(int64_t b, int64_t n, int remap) {
+template <typename I>
+__device__ __forceinline__ I tile_of(I b, I n, int remap) {
   if (!remap || (n & 7)) return b;
   return (b & 7) * (n >> 3) + (b >> 3);
 }
@@ -636,8 +637,8 @@ k_strip(PassArgs a) {
   __shared__ float2 lds[EX == 0 ? W * LY::LS : (W * LY::LS + 1) / 2];
 
   const int tid = threadIdx.x;
-  const int64_t tile = tile_of(blockIdx.x, a.total_tiles, a.xcd_remap);
-  const int64_t bat = tile >> a.batch_shift;
+  const uint32_t tile = tile_of((uint32_t)blockIdx.x, (uint32_t)a.total_tiles, a.xcd_remap);
+  const uint32_t bat = tile >> a.batch_shift;
   const int tile_in_batch = (int)(tile - (bat << a.batch_shift));
   const int line0 = tile_in_batch * W;
 
@@ -773,8 +774,8 @@ k_pipe(PassArgs a) {
     float2 lo, hi;
   };
   auto prefetch = [&](Pre& n, int64_t tl) {
-    const int64_t bat = tl >> a.batch_shift;
-    const int tib = (int)(tl - (bat << a.batch_shift));
+    const uint32_t bat = (uint32_t)tl >> a.batch_shift;
+    const int tib = (int)((uint32_t)tl - (bat << a.batch_shift));
     const int line0 = tib * W;
     const bool lmap = kLineMap<LOADM, STOREM>() && a.line_map;
     const int l0 = lmap ? 0 : line0;
@@ -821,8 +822,8 @@ k_pipe(PassArgs a) {
       }
       tw_base = cscale(cmul(n.hi, n.lo), a.scale);
     }
-    const int64_t bat = tile >> a.batch_shift;
-    const int tib = (int)(tile - (bat << a.batch_shift));
+    const uint32_t bat = (uint32_t)tile >> a.batch_shift;
+    const int tib = (int)((uint32_t)tile - (bat << a.batch_shift));
     const int line0 = tib * W;
     if (ahead < a.total_tiles) prefetch(n, ahead);
 
@@ -860,7 +861,7 @@ k_pipe(PassArgs a) {
   // tiles, so that neighbouring strips, which share cache lines when a row
   // segment is narrower than a line, are in flight on one L2 together
   const int64_t G = gridDim.x;
-  int64_t tile = tile_of(blockIdx.x, G, a.xcd_remap);
+  int64_t tile = tile_of((int64_t)blockIdx.x, G, a.xcd_remap);
   // The prologue's prefetch is drained before the walk starts, so that the
   // top of the loop sees the same memory state from the prologue as from
   // its back edge (the previous tile's stores in flight, its prefetch

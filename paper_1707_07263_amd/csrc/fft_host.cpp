@@ -682,7 +682,7 @@ int build_schedule_inner(const int64_t* n, int64_t batch, int dims, int dtype, c
       }
       if (f.v->W != r) return FFT_ERR_INVALID_ARGUMENT;
       int rc;
-      rc = choose(ov.col, ROLE_COL, (int)M, dtype, 16, C, r, &cl.v);
+      rc = choose(ov.col, ROLE_COL, (int)M, dtype, 16, r * C, batch, &cl.v);
       if (rc) return rc;
       if (M * batch > INT32_MAX) return FFT_ERR_UNSUPPORTED_SIZE;
       PassArgs& a = f.args;
@@ -698,16 +698,16 @@ int build_schedule_inner(const int64_t* n, int64_t batch, int dims, int dtype, c
       f.src = SEL_IN;
       f.dst = SEL_OUT;
       f.first = true;
-      // columns: line c, points k1 at stride r*C; block k2 starts at row k2
-      // (one image per launch when batched)
+      // columns: line k2*C + c is column c over rows r*k1 + k2, points k1 at
+      // stride r*C
       PassArgs& b = cl.args;
       b.in_line = b.out_line = 1;
       b.in_elem = b.out_elem = r * C;
-      b.in_batch = b.out_batch = C;
-      b.lines = (int32_t)C;
-      b.tiles_per_batch = (int32_t)((C + cl.v->W - 1) / cl.v->W);
-      b.total_tiles = (int64_t)b.tiles_per_batch * r;
-      cl.per_transform = true;
+      b.in_batch = b.out_batch = R * C;
+      b.lines = (int32_t)(r * C);
+      b.tiles_per_batch = (int32_t)((r * C + cl.v->W - 1) / cl.v->W);
+      b.total_tiles = (int64_t)b.tiles_per_batch * batch;
+      if (b.total_tiles > INT32_MAX) return FFT_ERR_UNSUPPORTED_SIZE;
       cl.src = SEL_OUT;
       cl.dst = SEL_OUT;
       cl.last = true;

@@ -188,8 +188,12 @@ def rowcol_set():
 # fused row passes whose stage twiddles come from two factor tables of W_L
 # (TWP 2): the LDS then holds a one-round exchange of four (or two) 4096-point
 # rows; two rows of 16 points per lane take 128 registers and 69 KB of LDS,
-# so two workgroups share a CU
-SPLIT_TW_ROWCOL = [(4096, 16, 4, 0, 2), (4096, 32, 4, 0, 2), (4096, 16, 2, 0, 2), (4096, 32, 2, 0, 2)]
+# so two workgroups share a CU.  Shorter rows take 16 or 8 points per lane the
+# same way (2048-point rows: 49-55 us per 2^24 points against 60-75 with 32
+# points per lane and the stage table in LDS; 1024: 51 against 57)
+SPLIT_TW_ROWCOL = [(4096, 16, 4, 0, 2), (4096, 32, 4, 0, 2), (4096, 16, 2, 0, 2), (4096, 32, 2, 0, 2),
+                   (2048, 16, 4, 0, 2), (2048, 16, 2, 0, 2), (1024, 16, 4, 0, 2), (512, 8, 4, 0, 2),
+                   (256, 8, 4, 0, 2)]
 
 
 def name(role, L, P, W, ex, dt, persist=0):

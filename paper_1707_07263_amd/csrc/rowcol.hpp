@@ -89,7 +89,7 @@ __global__ void __launch_bounds__((W * Sched<L, P>::T), 1) k_rowcol(PassArgs a) 
   };
 
   const int64_t G = gridDim.x;
-  int64_t tile = tile_of(blockIdx.x, G, a.xcd_remap);
+  int64_t tile = tile_of((int64_t)blockIdx.x, G, a.xcd_remap);
   if (tile < a.total_tiles) prefetch(tile);
   // drained here so that the top of the loop sees the same memory state on
   // its first pass as from its back edge (else its wait covers the stores)

@@ -114,3 +114,28 @@ def test_many_default_kernel(dev, sizes, schedule, dt):
             err = rel_l2_rows(got[at:at + n], ref[at:at + n], n).max()
             assert err <= {"c64": tol_fp32(n), "f16": 1e-3, "bf16": 8e-3}[dt], (n, inverse, float(err))
             at += n
+
+
+# images of 2048 rows and more through the Python layer: fused row passes of
+# every row length, a batch of several images in one column launch, columns
+# outside the rule, in place (by the plan's own exec too)
+@pytest.mark.parametrize("rows,cols,batch", [(2048, 256, 3), (2048, 1024, 2), (2048, 2048, 1), (2048, 4096, 2),
+                                             (4096, 512, 3), (4096, 2048, 1), (4096, 32, 3), (8192, 256, 2),
+                                             (16384, 256, 1)])
+@pytest.mark.parametrize("inverse", [False, True])
+def test_images_by_rule(dev, rows, cols, batch, inverse):
+    from paper_1707_07263_amd import api
+    n = rows * cols
+    x = workloads.normal_batch(n, batch, seed=rows + cols).reshape(batch, rows, cols)
+    xt = to_gpu_c64(x, dev)
+    ref = oracle.fft2(x.astype(np.complex64), inverse=inverse).reshape(batch, n)
+    got = api.fft2(xt, inverse=inverse)
+    assert rel_l2_rows(got.cpu().numpy().reshape(batch, n), ref, n).max() <= tol_fp32(n)
+    y = xt.clone()
+    api.fft2(y, inverse=inverse, out=y)
+    assert torch.equal(y, got)
+    api.clear_cache()
+    plan = api.get_plan([rows, cols], batch, capi.FFT_C64, capi.FFT_INVERSE if inverse else capi.FFT_FORWARD)
+    z = xt.clone()
+    plan.exec(z, z)
+    assert torch.equal(z, got)

@@ -58,3 +58,24 @@ def test_2d(dtype, lg_r):
                               and capi.fft_variant_describe(i)["L"] == L
                               and capi.fft_variant_describe(i)["dtype"] == dtype]
                     assert min(widths) > c, (r, c, names)
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+def test_2d_rule_plans_wherever_it_applies(dtype):
+    from paper_1707_07263_amd import autotune
+    ruled = 0
+    for lg_r in range(0, 15):
+        for lg_c in range(0, 15):
+            r, c = 1 << lg_r, 1 << lg_c
+            s = autotune.rule_for([r, c], dtype)
+            if s is None:
+                continue
+            ruled += 1
+            for batch in (1, 3, 1000):
+                d = capi.fft_describe([r, c], batch, 2, dtype, s)
+                p = [parse(x) for x in d["names"]]
+                assert d["passes"] == 2 and p[0][1] == c
+                assert p[0][0] == ("f" if "rowcol" in s else "r")
+                # what the fused row pass leaves of the columns
+                assert p[1][0] == "c" and p[1][1] * (p[0][2] if p[0][0] == "f" else 1) == r
+    assert ruled > 0
