@@ -152,6 +152,13 @@ template <int L, int P> struct Sched {
 template <int L> struct LdsLayout {
   static constexpr int LS = L + (L >> 5) + (L < 16 ? 1 : 2);
   __device__ __forceinline__ static int idx(int m, int e) { return m * LS + e + (e >> 5); }
+  // idx(m, e + c) = idx(m, e) + step(c) wherever adding c to e carries nothing
+  // out of its low five bits: c a multiple of 32, or c a multiple of a power
+  // of two that e's low bits stay below.  Every exchange here is of that kind
+  // (points t + q*T with t < T; outputs o0 + r*NS with o0 mod NS*R < NS), and
+  // the sums then are one base per lane and constant offsets, where the
+  // compiler computes and holds an address per point.
+  __host__ __device__ static constexpr int step(int c) { return c + (c >> 5); }
 };
 
 // ---------------------------------------------------------------------------
@@ -387,31 +394,24 @@ template <int L, int P> struct TwLds {
 // 16384-point line has 8192 or 16384 factors W^{k r}, each used once per
 // line: as a table they are 64 or 128 KB, as much as the line itself, which
 // neither fits in LDS beside the line nor is cheap to read from L2.  With
-// k = (k1 << H) + k0, W^{k r} = W^{(k1 << H) r} W^{k0 r}: two tables of about
-// sqrt(NS) rows of R factors, both rows of the stage table, and one complex
-// multiply per factor.  Stages of up to 32 rows keep their table.
+// k = (k1 << LP) + k0, LP = log2 of the radix, W_{NS R}^{k r} =
+// W_NS^{k1 r} W_{NS R}^{k0 r}: the first factor is the previous stage's table,
+// the second R rows of this one's, and each twiddle one complex multiply.
+// Other stages keep their table (16384 points, 32 per lane: 12.7 KB in all).
 template <int L, int P> struct TwFac {
   using S = Sched<L, P>;
-  static constexpr int H_MIN_NS = 64;
-  __host__ __device__ static constexpr bool split(int s) { return S::ns(s) >= H_MIN_NS; }
-  __host__ __device__ static constexpr int h(int s) { return (ilog2(S::ns(s)) + 1) / 2; }
+  __host__ __device__ static constexpr bool split(int s) { return s >= 2 && S::ns(s) > 128; }
   __host__ __device__ static constexpr int rp(int s) { return S::radix(s) >= 4 ? S::radix(s) + 1 : S::radix(s); }
-  __host__ __device__ static constexpr int rows(int s) {
-    return split(s) ? (1 << h(s)) + (S::ns(s) >> h(s)) : S::ns(s);
-  }
+  __host__ __device__ static constexpr int rows(int s) { return split(s) ? S::PP : S::ns(s); }
   __host__ __device__ static constexpr int off(int s) { return s <= 1 ? 0 : off(s - 1) + rows(s - 1) * rp(s - 1); }
   static constexpr int SIZE = off(S::S) > 0 ? off(S::S) : 1;
   template <int s = 1>
   __device__ __forceinline__ static void copy(float2* dst, const float2* __restrict__ src, int tid, int nt) {
     if constexpr (s < S::S) {
+      static_assert(!split(s) || (!split(s - 1) && S::radix(s - 1) == S::PP), "the previous stage keeps its table");
       constexpr int R = S::radix(s);
-      for (int i = tid; i < rows(s) * R; i += nt) {
-        const int row = i / R, r = i % R;
-        int k = row;
-        if constexpr (split(s))
-          if (row >= (1 << h(s))) k = (row - (1 << h(s))) << h(s);
-        dst[off(s) + row * rp(s) + r] = src[S::off(s) + k * R + r];
-      }
+      for (int i = tid; i < rows(s) * R; i += nt)
+        dst[off(s) + (i / R) * rp(s) + i % R] = src[S::off(s) + i];
       copy<s + 1>(dst, src, tid, nt);
     }
   }
@@ -426,39 +426,47 @@ template <int L, int P> struct TwFac {
 // half the size (twice the barriers, half the LDS, so twice the workgroups
 // fit on a CU).
 // ---------------------------------------------------------------------------
-template <int L, int PP, int EX, int R, int NS>
+// LEAN: each point read by an address of its own.  From one base the compiler
+// pairs the reads, and a pair returns into four adjacent registers: in the
+// passes with two tiles in flight, which use nearly all 256, that spills
+// (1024-point first pass 53.5 -> 54.9 us).
+template <int L, int PP, int EX, int R, int NS, bool LEAN = false>
 __device__ __forceinline__ void exchange(float2* v, void* ldsv, int m, int m2, int t2, const int* o0) {
   using LY = LdsLayout<L>;
   constexpr int T = L / PP;
   constexpr int NB = PP / R;
+  int wr[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) wr[b] = LY::idx(m, o0[b]);
+  const int rd = LY::idx(m2, t2);
   if constexpr (EX == 0) {
     float2* lds = reinterpret_cast<float2*>(ldsv);
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int r = 0; r < R; ++r) lds[LY::idx(m, o0[b] + r * NS)] = v[b + r * NB];
+      for (int r = 0; r < R; ++r) lds[wr[b] + LY::step(r * NS)] = v[b + r * NB];
     lds_barrier();
 #pragma unroll
-    for (int q = 0; q < PP; ++q) v[q] = lds[LY::idx(m2, t2 + q * T)];
+    for (int q = 0; q < PP; ++q) v[q] = lds[LEAN ? LY::idx(m2, t2 + q * T) : rd + LY::step(q * T)];
     lds_barrier();
   } else {
     float* lds = reinterpret_cast<float*>(ldsv);
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int r = 0; r < R; ++r) lds[LY::idx(m, o0[b] + r * NS)] = v[b + r * NB].x;
+      for (int r = 0; r < R; ++r) lds[wr[b] + LY::step(r * NS)] = v[b + r * NB].x;
     lds_barrier();
     // the real parts are dead once written: reuse their registers
 #pragma unroll
-    for (int q = 0; q < PP; ++q) v[q].x = lds[LY::idx(m2, t2 + q * T)];
+    for (int q = 0; q < PP; ++q) v[q].x = lds[rd + LY::step(q * T)];
     lds_barrier();
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int r = 0; r < R; ++r) lds[LY::idx(m, o0[b] + r * NS)] = v[b + r * NB].y;
+      for (int r = 0; r < R; ++r) lds[wr[b] + LY::step(r * NS)] = v[b + r * NB].y;
     lds_barrier();
 #pragma unroll
-    for (int q = 0; q < PP; ++q) v[q].y = lds[LY::idx(m2, t2 + q * T)];
+    for (int q = 0; q < PP; ++q) v[q].y = lds[rd + LY::step(q * T)];
     lds_barrier();
   }
 }
@@ -499,7 +507,7 @@ template <int L, int P, int s, int TWP> struct StageTw {
   }
 };
 
-template <int L, int P, int EX, int s, int TWP = 0>
+template <int L, int P, int EX, int s, int TWP = 0, bool LEAN = false>
 struct Stage {
   using S = Sched<L, P>;
   using TW = StageTw<L, P, s, TWP>;
@@ -537,9 +545,8 @@ struct Stage {
         }
       } else if constexpr (s > 0 && TWP == 3 && TwFac<L, P>::split(s)) {
         using TF = TwFac<L, P>;
-        constexpr int H = TF::h(s);
-        const float2* lo = twt + TF::off(s) + (k & ((1 << H) - 1)) * TF::rp(s);
-        const float2* hi = twt + TF::off(s) + ((1 << H) + (k >> H)) * TF::rp(s);
+        const float2* lo = twt + TF::off(s) + (k & (R - 1)) * TF::rp(s);
+        const float2* hi = twt + TF::off(s - 1) + (k / R) * TF::rp(s - 1);
 #pragma unroll
         for (int r = 1; r < R; ++r) x[r] = cmul(x[r], cmul(hi[r], lo[r]));
       } else if constexpr (s > 0) {
@@ -555,22 +562,22 @@ struct Stage {
       for (int r = 0; r < R; ++r) v[b + r * NB] = x[r];
     }
     if constexpr (s < S::S - 1) {
-      exchange<L, PP, EX, R, NS>(v, lds, m, m_st, t_st, o0);
+      exchange<L, PP, EX, R, NS, LEAN>(v, lds, m, m_st, t_st, o0);
       m = m_st;
       t = t_st;
-      Stage<L, P, EX, s + 1, TWP>::run(v, lds, m, t, m_st, t_st, twt, next);
+      Stage<L, P, EX, s + 1, TWP, LEAN>::run(v, lds, m, t, m_st, t_st, twt, next);
     }
   }
 };
 
-template <int L, int P, int W, int EX, int TWP = 0>
+template <int L, int P, int W, int EX, int TWP = 0, bool LEAN = false>
 __device__ __forceinline__ void run_stages(float2* v, void* lds, int& m, int& t,
                                            int m_st, int t_st, bool remap,
                                            const float2* __restrict__ twt) {
   using S = Sched<L, P>;
   constexpr int T = S::T;
   constexpr int PP = S::PP;
-  Stage<L, P, EX, 0, TWP>::run(v, lds, m, t, m_st, t_st, twt, StageTw<L, P, 0, TWP>());
+  Stage<L, P, EX, 0, TWP, LEAN>::run(v, lds, m, t, m_st, t_st, twt, StageTw<L, P, 0, TWP>());
   if constexpr (S::S == 1) {
     if (remap) {
       // one-stage transform whose load and store mappings differ: transpose
@@ -828,7 +835,7 @@ k_pipe(PassArgs a) {
     if (ahead < a.total_tiles) prefetch(n, ahead);
 
     int m = m_ld, t = t_ld;
-    run_stages<L, P, W, EX, kPipeTwp<L>>(v, xch, m, t, m_st, t_st, LOADM != STOREM, twl);
+    run_stages<L, P, W, EX, kPipeTwp<L>, DEPTH == 2>(v, xch, m, t, m_st, t_st, LOADM != STOREM, twl);
     if (TWID) lds_barrier();  // step rows visible (also when no exchange ran)
 
     const bool lmap = kLineMap<LOADM, STOREM>() && a.line_map;

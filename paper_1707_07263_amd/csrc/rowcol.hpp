@@ -121,32 +121,33 @@ __global__ void __launch_bounds__((W * Sched<L, P>::T), 1) k_rowcol(PassArgs a) 
     // column step: lane tid takes columns c = tid + i*NT of every row j,
     // v[j*CPL + i] <- row j, column c (the exchange buffer is free: the
     // stages end with a barrier after their last LDS read)
+    const int wr = LY::idx(m, t), rd = LY::idx(0, tid);
     if constexpr (EX == 0) {
 #pragma unroll
-      for (int q = 0; q < PP; ++q) xch[LY::idx(m, t + q * T)] = v[q];
+      for (int q = 0; q < PP; ++q) xch[wr + LY::step(q * T)] = v[q];
       lds_barrier();
 #pragma unroll
       for (int j = 0; j < W; ++j)
 #pragma unroll
-        for (int i = 0; i < CPL; ++i) v[j * CPL + i] = xch[LY::idx(j, tid + i * NT)];
+        for (int i = 0; i < CPL; ++i) v[j * CPL + i] = xch[rd + j * LY::LS + LY::step(i * NT)];
     } else {
       float* xf = reinterpret_cast<float*>(xch);
 #pragma unroll
-      for (int q = 0; q < PP; ++q) xf[LY::idx(m, t + q * T)] = v[q].x;
+      for (int q = 0; q < PP; ++q) xf[wr + LY::step(q * T)] = v[q].x;
       lds_barrier();
       // the real parts are dead once written: reuse their registers
 #pragma unroll
       for (int j = 0; j < W; ++j)
 #pragma unroll
-        for (int i = 0; i < CPL; ++i) v[j * CPL + i].x = xf[LY::idx(j, tid + i * NT)];
+        for (int i = 0; i < CPL; ++i) v[j * CPL + i].x = xf[rd + j * LY::LS + LY::step(i * NT)];
       lds_barrier();
 #pragma unroll
-      for (int q = 0; q < PP; ++q) xf[LY::idx(m, t + q * T)] = v[q].y;
+      for (int q = 0; q < PP; ++q) xf[wr + LY::step(q * T)] = v[q].y;
       lds_barrier();
 #pragma unroll
       for (int j = 0; j < W; ++j)
 #pragma unroll
-        for (int i = 0; i < CPL; ++i) v[j * CPL + i].y = xf[LY::idx(j, tid + i * NT)];
+        for (int i = 0; i < CPL; ++i) v[j * CPL + i].y = xf[rd + j * LY::LS + LY::step(i * NT)];
     }
     TS* dst = reinterpret_cast<TS*>(a.out) + b * a.out_batch + (W * n1) * a.out_line;
 #pragma unroll
