@@ -317,16 +317,20 @@ template <typename TS> struct Strip {
     else if constexpr (std::is_same<TS, __half2>::value) return __half22float2(__builtin_bit_cast(__half2, x));
     else return make_float2(__uint_as_float(x << 16), __uint_as_float(x & 0xffff0000u));
   }
-  __device__ __forceinline__ void store(uint32_t lane, uint32_t uni, float2 v) const {
+  __device__ __forceinline__ static Raw raw(float2 v) {
+    if constexpr (sizeof(TS) == 8) return v;
+    else if constexpr (std::is_same<TS, __half2>::value) return pack_f16x2(v.x, v.y);
+    else return pack_bf16x2(v.x, v.y);
+  }
+  __device__ __forceinline__ void store_raw(uint32_t lane, uint32_t uni, Raw x) const {
     if constexpr (sizeof(TS) == 8) {
       typedef uint32_t u2v __attribute__((ext_vector_type(2)));
-      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2v, v), r, lane, uni, 0);
-    } else if constexpr (std::is_same<TS, __half2>::value) {
-      __builtin_amdgcn_raw_buffer_store_b32(pack_f16x2(v.x, v.y), r, lane, uni, 0);
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2v, x), r, lane, uni, 0);
     } else {
-      __builtin_amdgcn_raw_buffer_store_b32(pack_bf16x2(v.x, v.y), r, lane, uni, 0);
+      __builtin_amdgcn_raw_buffer_store_b32(x, r, lane, uni, 0);
     }
   }
+  __device__ __forceinline__ void store(uint32_t lane, uint32_t uni, float2 v) const { store_raw(lane, uni, raw(v)); }
 };
 
 // Map a workgroup id to a tile so that tiles t, t+1, ... run on the same XCD
@@ -623,6 +627,21 @@ __host__ __device__ constexpr bool kLineMap() {
   return LOADM == 0 && STOREM == 0;
 }
 
+// Short rows: a lane's points of a line are T apart and a load of the wave
+// touches T neighbouring points of each line, so with few lanes per line every
+// load and store reaches into many lines for a fraction of each.  The tile is
+// one contiguous run: it is loaded and stored in order instead and takes two
+// more turns through LDS, in its storage type.  Per 2^24 points, before and
+// after: fp16 rows of 16 points 66 and 25 us, of 32 40 and 26, of 64 32 and 26;
+// complex64 of 8 97 and 46, of 16 64 and 46, of 64 48.7 and 46.2.  Up to 8 lanes
+// per line (fp16 rows of 128 points, 16 lanes: 28.6 without, 29.7 with).
+// (One-round exchanges only: their LDS holds the tile with a slot per line to
+// spare, LdsLayout's stride being at least L + 1.)
+template <int LOADM, int STOREM, int EX, int T>
+__host__ __device__ constexpr bool kStagedRows() {
+  return LOADM == 0 && STOREM == 0 && EX == 0 && T <= 8;
+}
+
 template <int L, int P, int W, int EX>
 __host__ __device__ constexpr int strip_min_waves() {
   constexpr int nt = W * Sched<L, P>::T;
@@ -656,7 +675,31 @@ k_strip(PassArgs a) {
   const bool lmap = kLineMap<LOADM, STOREM>() && a.line_map;
 
   float2 v[PP];
-  {
+  using Raw = typename Strip<TS>::Raw;
+  constexpr int NT = W * T;
+  // in order when the rows are: no line map, no blocked output
+  const bool staged = kStagedRows<LOADM, STOREM, EX, T>() && !lmap && !a.blk_lg;
+  Raw* const flat = reinterpret_cast<Raw*>(lds);  // point i of line m at m*(L + 1) + i
+  const int held = min(W, a.lines - line0) * L;   // points of the tile
+  if (kStagedRows<LOADM, STOREM, EX, T>() && staged) {
+    const Strip<TS> src(reinterpret_cast<const TS*>(a.in) + bat * a.in_batch + (int64_t)line0 * L);
+    const uint32_t sgn = a.conj_in ? 0x80000000u : 0u;
+    Raw x[PP];
+#pragma unroll
+    for (int q = 0; q < PP; ++q) x[q] = src.load_raw(min(tid + q * NT, held - 1) * (uint32_t)sizeof(TS), 0);
+#pragma unroll
+    for (int q = 0; q < PP; ++q) {
+      const int e = tid + q * NT;
+      flat[e / L * (L + 1) + e % L] = x[q];
+    }
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < PP; ++q) {
+      v[q] = src.value(flat[m * (L + 1) + t + q * T]);
+      v[q].y = __uint_as_float(__float_as_uint(v[q].y) ^ sgn);
+    }
+    lds_barrier();
+  } else {
     // lines past the end of a partial strip load a valid line and are not stored
     const int l0 = lmap ? 0 : line0;
     const int ln = (lmap ? a.line_map[tile_in_batch * W + m] : min(line0 + m, a.lines - 1)) - l0;
@@ -674,7 +717,19 @@ k_strip(PassArgs a) {
   run_stages<L, P, W, EX>(v, lds, m, t, m_st, t_st, LOADM != STOREM, a.tw);
 
   // epilogue: inter-pass twiddle, scale, conjugate, store
-  {
+  if (kStagedRows<LOADM, STOREM, EX, T>() && staged) {
+    const Strip<TS> dst(reinterpret_cast<TS*>(a.out) + bat * a.out_batch + (int64_t)line0 * L);
+    const float scale_im = a.conj_out ? -a.scale : a.scale;
+#pragma unroll
+    for (int q = 0; q < PP; ++q)
+      flat[m * (L + 1) + t + q * T] = dst.raw(make_float2(v[q].x * a.scale, v[q].y * scale_im));
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < PP; ++q) {
+      const int e = tid + q * NT;
+      if (e < held) dst.store_raw(e * (uint32_t)sizeof(TS), 0, flat[e / L * (L + 1) + e % L]);
+    }
+  } else {
     const int line = lmap ? row_transpose(a.line_map[tile_in_batch * W + m], a.tr_shift) : line0 + m;
     const bool ok = lmap || line < a.lines;
     const int l0 = lmap ? 0 : line0;

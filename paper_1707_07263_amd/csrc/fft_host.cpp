@@ -118,7 +118,7 @@ size_t esize(int dtype) { return dtype == FFT_C64 ? 8 : 4; }
 // flight (51-54 against 53-58 us; with 2 tiles per CU it is the other way
 // round, 12.5 against 10.4 us for 2^21 points).  Longer rows hold one line per
 // workgroup; their stage twiddles come from factor tables in LDS and the next
-// line is in flight (16384: 82 us against 116).  Short rows take 512 lanes.
+// line is in flight (16384: 82 us against 116).
 //
 // Columns and first passes of a split: as wide as LDS and registers allow
 // while there are tiles for every CU (two for every CU where a tile of 32
@@ -136,8 +136,8 @@ struct Pref {
 };
 constexpr int64_t kCus = 256;  // MI355X
 constexpr Pref kPrefs[] = {
-    {ROLE_ROW, 32, 16, 8, 256, 0, 0, 0},
-    {ROLE_ROW, 32, 32, 8, 128, 0, 0, 0},
+    {ROLE_ROW, 32, 16, 8, 128, 0, 0, 0},
+    {ROLE_ROW, 32, 32, 8, 64, 0, 0, 0},
     {ROLE_ROW, 32, 64, 8, 32, 0, 0, 0},
     {ROLE_ROW, 32, 128, 8, 16, 0, 0, 0},
     {ROLE_ROW, 32, 256, 8, 8, 0, 0, 0},
@@ -150,8 +150,8 @@ constexpr Pref kPrefs[] = {
     {ROLE_ROW, 32, 4096, 8, 1, 0, 0, 0},
     {ROLE_ROW, 32, 8192, 16, 1, 1, 0, 0},
     {ROLE_ROW, 32, 16384, 32, 1, 1, 0, 0},
-    {ROLE_ROW, 16, 16, 8, 256, 0, 0, 0},
-    {ROLE_ROW, 16, 32, 8, 128, 0, 0, 0},
+    {ROLE_ROW, 16, 16, 8, 128, 0, 0, 0},
+    {ROLE_ROW, 16, 32, 8, 64, 0, 0, 0},
     {ROLE_ROW, 16, 64, 8, 32, 0, 0, 0},
     {ROLE_ROW, 16, 128, 8, 16, 0, 0, 0},
     {ROLE_ROW, 16, 256, 8, 8, 0, 0, 0},

@@ -137,8 +137,7 @@ def c16_set():
     for lg in range(11, 13):
         if ok(1 << lg, 16, 2):
             out.append(("r", 1 << lg, 16, 2, 0))
-    # rows with 8 points per lane and 256 lanes (512 for short lines, whose
-    # loads then cover more of a line group; whole lines of 4096 and 8192)
+    # rows with 8 points per lane and 256 or 512 lanes (1024 for lines of 8192)
     for lg in range(4, 14):
         L = 1 << lg
         for target in (256, 512):

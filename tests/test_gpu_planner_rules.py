@@ -43,6 +43,7 @@ def check(dev, shape, batch, dt, inverse, schedule=None):
 # persistent kernel (8 tiles for each of 256 CUs) and the first at it, plus a
 # ragged tile; for the longest lines a persistent walk of more than one round
 ROWS = [(n, b) for n in (2, 8, 16, 32, 64, 256, 512) for b in (1, 37)]
+ROWS += [(4, 1000), (16, 1000), (32, 1001), (64, 4097)]  # short rows: whole tiles and a partial one
 ROWS += [(1024, 1), (1024, 8188), (1024, 8189), (2048, 3), (2048, 4094), (2048, 4095), (4096, 1), (4096, 2047),
          (4096, 2048), (8192, 1), (8192, 259), (16384, 1), (16384, 259)]
 
