@@ -714,6 +714,28 @@ k_strip(PassArgs a) {
     }
   }
 
+  // inter-pass twiddle W_N^{row*(t + q*T)} = W_N^{row*t} * W_N^{row*q*T}
+  // (row = line >> tw_line_shift): one base per lane, and a step row shared by
+  // the lanes of a line.  With 8 points per lane, the variants for few tiles,
+  // they are read ahead of the butterflies: nothing else on the CU hides
+  // their latency there.
+  constexpr bool TW_AHEAD = TWID && PP <= 8;
+  float2 tw_lo = make_float2(1.f, 0.f), tw_hi = tw_lo;
+  float2 tw_steps[TW_AHEAD ? PP : 1];
+  const float2* tw_row = a.tw_step;
+  auto load_twiddles = [&]() {
+    const uint32_t row = (uint32_t)min(line0 + m_st, a.lines - 1) >> a.tw_line_shift;
+    const uint32_t jb = row * (uint32_t)t_st;
+    tw_hi = a.tw_hi[jb >> a.tw_shift];
+    tw_lo = a.tw_lo[jb & (uint32_t)a.tw_mask];
+    tw_row = a.tw_step + (int64_t)row * PP;
+  };
+  if constexpr (TW_AHEAD) {
+    load_twiddles();
+#pragma unroll
+    for (int q = 0; q < PP; ++q) tw_steps[q] = tw_row[q];
+  }
+
   run_stages<L, P, W, EX>(v, lds, m, t, m_st, t_st, LOADM != STOREM, a.tw);
 
   // epilogue: inter-pass twiddle, scale, conjugate, store
@@ -742,23 +764,17 @@ k_strip(PassArgs a) {
       step = (uint32_t)(T * sizeof(TS)) << a.blk_rows_lg;
     }
     const Strip<TS> dst(base);
-    // inter-pass twiddle W_N^{row*(t + q*T)} = W_N^{row*t} * W_N^{row*q*T}
-    // (row = line >> tw_line_shift): one base per lane, and a step row
-    // shared by the lanes of a line
     float2 tw_base = make_float2(1.f, 0.f);
-    const float2* tw_row = a.tw_step;
-    if (TWID && ok) {
-      const uint32_t row = (uint32_t)line >> a.tw_line_shift;
-      const uint32_t jb = row * (uint32_t)t;
-      tw_base = cmul(a.tw_hi[jb >> a.tw_shift], a.tw_lo[jb & (uint32_t)a.tw_mask]);
-      tw_base = cscale(tw_base, a.scale);
-      tw_row = a.tw_step + (int64_t)row * PP;
+    if constexpr (TWID) {
+      if constexpr (!TW_AHEAD) load_twiddles();
+      tw_base = cscale(cmul(tw_hi, tw_lo), a.scale);
     }
     const float scale_im = a.conj_out ? -a.scale : a.scale;
     if (ok) {
 #pragma unroll
       for (int q = 0; q < PP; ++q)
-        dst.store(off, q * step, out_value<TWID>(v[q], tw_base, TWID ? tw_row[q] : tw_base, a.scale, scale_im));
+        dst.store(off, q * step, out_value<TWID>(v[q], tw_base, TW_AHEAD ? tw_steps[q] : TWID ? tw_row[q] : tw_base, a.scale,
+                                              scale_im));
     }
   }
 }

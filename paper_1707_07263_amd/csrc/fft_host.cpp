@@ -123,9 +123,12 @@ size_t esize(int dtype) { return dtype == FFT_C64 ? 8 : 4; }
 // Columns and first passes of a split: as wide as LDS and registers allow
 // while there are tiles for every CU (two for every CU where a tile of 32
 // lines halves the number), narrower below, since an idle CU costs more than
-// a short row segment (2^20 points in all, 1024-point first pass: 8.4 us with
+// a short row segment (2^20 points in all, 1024-point first pass: 8.0 us with
 // 4 columns per tile against 19 with 16).  First passes are persistent, with
-// the next one or two tiles in flight; second passes alternate two
+// the next one or two tiles in flight, where a CU gets several tiles; with one
+// tile or less they run 8 points per lane, one tile per workgroup, their
+// twiddles read ahead (2^16 points: 5.6-6.2 us against 6.7-7.7; 2^18: 5.9-6.4
+// against 7.5-7.9).  Second passes alternate two
 // workgroups per CU with the two-round exchange instead (1024 points: 42 us
 // against 59 with 16 points per lane and one workgroup).
 // ---------------------------------------------------------------------------
@@ -166,11 +169,12 @@ constexpr Pref kPrefs[] = {
     {ROLE_SPLIT_A, 32, 128, 8, 16, 0, 0, kCus},
     {ROLE_SPLIT_A, 32, 128, 8, 8, 0, 0, 0},
     {ROLE_SPLIT_A, 32, 256, 16, 32, 1, 0, 2 * kCus},
-    {ROLE_SPLIT_A, 32, 256, 16, 16, 1, 0, kCus},
+    {ROLE_SPLIT_A, 32, 256, 16, 16, 1, 0, 2 * kCus},
+    {ROLE_SPLIT_A, 32, 256, 8, 8, 0, 0, kCus},
     {ROLE_SPLIT_A, 32, 256, 8, 4, 0, 0, 0},
     {ROLE_SPLIT_A, 32, 512, 32, 32, 2, 0, 2 * kCus},
     {ROLE_SPLIT_A, 32, 512, 32, 16, 2, 0, kCus},
-    {ROLE_SPLIT_A, 32, 512, 16, 8, 2, 0, kCus / 2},
+    {ROLE_SPLIT_A, 32, 512, 8, 8, 0, 0, kCus / 2},
     {ROLE_SPLIT_A, 32, 512, 8, 4, 0, 0, 0},
     {ROLE_SPLIT_A, 32, 1024, 32, 16, 2, 0, kCus},
     {ROLE_SPLIT_A, 32, 1024, 8, 4, 0, 0, 0},
@@ -180,12 +184,15 @@ constexpr Pref kPrefs[] = {
     {ROLE_SPLIT_A, 16, 128, 16, 64, 1, 0, 2 * kCus},
     {ROLE_SPLIT_A, 16, 128, 16, 32, 1, 0, 0},
     {ROLE_SPLIT_A, 16, 256, 16, 32, 1, 0, kCus},
-    {ROLE_SPLIT_A, 16, 256, 16, 16, 1, 0, 0},
+    {ROLE_SPLIT_A, 16, 256, 16, 16, 1, 0, 3 * kCus / 4},
+    {ROLE_SPLIT_A, 16, 256, 8, 4, 0, 0, 0},
     {ROLE_SPLIT_A, 16, 512, 32, 32, 1, 0, 2 * kCus},
     {ROLE_SPLIT_A, 16, 512, 8, 16, 1, 0, kCus},
-    {ROLE_SPLIT_A, 16, 512, 8, 8, 1, 0, 0},
+    {ROLE_SPLIT_A, 16, 512, 8, 8, 0, 0, kCus},
+    {ROLE_SPLIT_A, 16, 512, 8, 4, 0, 0, 0},
     {ROLE_SPLIT_A, 16, 1024, 32, 16, 1, 0, kCus},
-    {ROLE_SPLIT_A, 16, 1024, 16, 8, 1, 0, 0},
+    {ROLE_SPLIT_A, 16, 1024, 16, 8, 1, 0, kCus},
+    {ROLE_SPLIT_A, 16, 1024, 8, 4, 0, 0, 0},
     {ROLE_SPLIT_A, 16, 2048, 16, 8, 1, 0, kCus},
     {ROLE_SPLIT_A, 16, 2048, 16, 4, 1, 0, 0},
     {ROLE_SPLIT_A, 16, 4096, 32, 8, 0, 1, kCus},

@@ -156,6 +156,7 @@ def c16_set():
             ("a", 1024, 32, 16, 0, 1), ("a", 1024, 32, 16, 0, 2), ("a", 1024, 16, 8, 0, 1),
             ("a", 2048, 16, 8, 0, 1), ("a", 2048, 16, 4, 0, 1),
             ("a", 4096, 32, 8, 1),
+            ("a", 256, 8, 4, 0), ("a", 512, 8, 8, 0), ("a", 512, 8, 4, 0), ("a", 1024, 8, 4, 0),
             ("c", 256, 16, 32, 0, 1), ("c", 256, 16, 32, 0), ("c", 256, 16, 8, 0),
             ("c", 512, 32, 16, 1), ("c", 512, 8, 16, 0), ("c", 512, 8, 8, 0),
             ("c", 1024, 32, 16, 1), ("c", 1024, 32, 16, 1, 1), ("c", 1024, 32, 8, 0),
