@@ -104,7 +104,9 @@ int fft_plan(const int64_t *n, int64_t batch, int dims, int dtype, int direction
  *                                       per pass, first pass first; 1: consecutive
  *                                       tiles run on one XCD, sharing its L2.
  *                                       Persistent variants ('q'): the workgroups
- *                                       of one XCD start on consecutive tiles)
+ *                                       of one XCD start on consecutive tiles.
+ *                                       Without the key: 1 for passes whose
+ *                                       strips are narrower than a 128 B line)
  *             | 'col3=' 0|1           (2-D: columns as two sub-passes of sqrt(rows)
  *                                       points; rows a power of 4, at least 2 columns)
  *             | 'colt=' variant       (the first of those sub-passes)
