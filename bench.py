@@ -442,7 +442,7 @@ def configs_report(capi, torch, reps):
     grouped = [(c, n) for n, c in sorted(counts.items())]
     for dt, name in ((C64, "complex64"), (capi.FFT_C16F, "fp16 pairs"), (capi.FFT_C16BF, "bf16 pairs")):
         h = capi.fft_plan_many_ex(sizes, dt, capi.FFT_FORWARD, autotune.many_schedule_for(sizes, dt))
-        add(f"512 uneven 2^8..2^16 in one exec (persistent kernel, two launches), {name}", [(h, sum(sizes) * (8 if dt == C64 else 4))],
+        add(f"512 uneven 2^8..2^16 in one exec (two launches), {name}", [(h, sum(sizes) * (8 if dt == C64 else 4))],
             8 if dt == C64 else 4,
             vendor=((lambda *xs: [tf.fft(x) for x in xs]), grouped, "fft per length (9 batched calls)")
             if dt == C64 else None)
