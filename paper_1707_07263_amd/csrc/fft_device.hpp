@@ -361,9 +361,24 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Entries of the two factor tables of W_L (TWP 2): 2^LA + 2^(log2 L - LA).
+// A twiddle as the product a b of two factors, b of a small angle.  b is held as
+// b - 1, whose rounding is that of a small number, a with the rest that its own
+// rounding left, and the product taken as a + (a (b - 1) + rest): only the last
+// sum is rounded at the size of a, so that the twiddle is as good as one read
+// from a table (rounded factors multiplied out had cost 2 to 10% of the whole
+// transform's error).
+__device__ __forceinline__ float2 tw_minus_one(float2 w) {
+  // cos - 1 = -sin^2 / (1 + cos), without the cancellation
+  return make_float2(-w.y * w.y / (1.0f + w.x), w.y);
+}
+__device__ __forceinline__ float2 tw_product(float2 a, float2 rest, float2 b1) {
+  return make_float2(a.x + fmaf(a.x, b1.x, fmaf(-a.y, b1.y, rest.x)),
+                     a.y + fmaf(a.x, b1.y, fmaf(a.y, b1.x, rest.y)));
+}
+
+// Entries of the two factor tables of W_L (TWP 2): 2^LA, and twice 2^(log2 L - LA).
 __host__ __device__ constexpr int tw_split_entries(int L) {
-  return (1 << ((ilog2(L) + 1) / 2)) + (1 << (ilog2(L) - (ilog2(L) + 1) / 2));
+  return (1 << ((ilog2(L) + 1) / 2)) + (2 << (ilog2(L) - (ilog2(L) + 1) / 2));
 }
 
 // Stage twiddles staged in LDS: the same entries as the global table, with
@@ -400,22 +415,30 @@ template <int L, int P> struct TwLds {
 // neither fits in LDS beside the line nor is cheap to read from L2.  With
 // k = (k1 << LP) + k0, LP = log2 of the radix, W_{NS R}^{k r} =
 // W_NS^{k1 r} W_{NS R}^{k0 r}: the first factor is the previous stage's table,
-// the second R rows of this one's, and each twiddle one complex multiply.
-// Other stages keep their table (16384 points, 32 per lane: 12.7 KB in all).
+// the second R rows of this one's (tw_product; the global table has the first
+// one's rests behind its last stage).  Other stages keep their table (16384
+// points, 32 per lane: 17 KB in all).
 template <int L, int P> struct TwFac {
   using S = Sched<L, P>;
   __host__ __device__ static constexpr bool split(int s) { return s >= 2 && S::ns(s) > 128; }
   __host__ __device__ static constexpr int rp(int s) { return S::radix(s) >= 4 ? S::radix(s) + 1 : S::radix(s); }
   __host__ __device__ static constexpr int rows(int s) { return split(s) ? S::PP : S::ns(s); }
   __host__ __device__ static constexpr int off(int s) { return s <= 1 ? 0 : off(s - 1) + rows(s - 1) * rp(s - 1); }
-  static constexpr int SIZE = off(S::S) > 0 ? off(S::S) : 1;
+  // the rests of the last but one stage's entries, rows laid out like theirs
+  static constexpr int REST = off(S::S);
+  static constexpr int SIZE = REST + S::ns(S::S - 2) * rp(S::S - 2);
   template <int s = 1>
   __device__ __forceinline__ static void copy(float2* dst, const float2* __restrict__ src, int tid, int nt) {
     if constexpr (s < S::S) {
-      static_assert(!split(s) || (!split(s - 1) && S::radix(s - 1) == S::PP), "the previous stage keeps its table");
+      static_assert(split(s) == (s == S::S - 1) && (s == 1 || S::radix(s - 1) == S::PP),
+                    "only the last stage is split, its previous one a table of the same radix");
       constexpr int R = S::radix(s);
-      for (int i = tid; i < rows(s) * R; i += nt)
-        dst[off(s) + (i / R) * rp(s) + i % R] = src[S::off(s) + i];
+      for (int i = tid; i < rows(s) * R; i += nt) {
+        const float2 w = src[S::off(s) + i];
+        dst[off(s) + (i / R) * rp(s) + i % R] = split(s) ? tw_minus_one(w) : w;
+      }
+      if constexpr (s == S::S - 2)
+        for (int i = tid; i < rows(s) * R; i += nt) dst[REST + (i / R) * rp(s) + i % R] = src[S::TW + i];
       copy<s + 1>(dst, src, tid, nt);
     }
   }
@@ -538,21 +561,28 @@ struct Stage {
         for (int r = 1; r < R; ++r) x[r] = cmul(x[r], ahead.w[b * R + r]);
       } else if constexpr (s > 0 && TWP == 2) {
         // TWP 2: W_{NS*R}^{k r} = W_L^e, e = k r L/(NS R), from two factor
-        // tables in LDS, twt[i] = W_L^i (i < 2^LA) and
-        // twt[2^LA + i] = W_L^{i 2^LA}: a few hundred bytes instead of the
-        // stage table
+        // tables in LDS, twt[i] = W_L^i - 1 (i < 2^LA) and
+        // twt[2^LA + i] = W_L^{i 2^LA} with its rest 2^(LG-LA) entries further
+        // on: about a kilobyte instead of the stage table
         constexpr int LG = ilog2(L), LA = (LG + 1) / 2, SC = L / (NS * R);
 #pragma unroll
         for (int r = 1; r < R; ++r) {
           const int e = k * r * SC;
-          x[r] = cmul(x[r], cmul(twt[e & ((1 << LA) - 1)], twt[(1 << LA) + (e >> LA)]));
+          const float2* hi = twt + (1 << LA) + (e >> LA);
+          x[r] = cmul(x[r], tw_product(hi[0], hi[1 << (LG - LA)], twt[e & ((1 << LA) - 1)]));
         }
       } else if constexpr (s > 0 && TWP == 3 && TwFac<L, P>::split(s)) {
         using TF = TwFac<L, P>;
         const float2* lo = twt + TF::off(s) + (k & (R - 1)) * TF::rp(s);
         const float2* hi = twt + TF::off(s - 1) + (k / R) * TF::rp(s - 1);
+        const float2* rest = hi + (TF::REST - TF::off(s - 1));
 #pragma unroll
-        for (int r = 1; r < R; ++r) x[r] = cmul(x[r], cmul(hi[r], lo[r]));
+        for (int r = 1; r < R; ++r) {
+          x[r] = cmul(x[r], tw_product(hi[r], rest[r], lo[r]));
+          // in order: else the reads of all factors come first, and 16384
+          // points spill 68 registers (109 us per 2^24 points against 73)
+          asm volatile("" : "+v"(x[r].x), "+v"(x[r].y));
+        }
       } else if constexpr (s > 0) {
         // TWP 0: global table; TWP 1 and 3: LDS copy with padded rows
         const float2* tw = TWP == 0   ? twt + S::off(s) + k * R

@@ -904,13 +904,14 @@ struct TableBuild {
   std::vector<TwSeg> segs;
   int64_t total = 0;
   std::map<std::pair<int, int>, int64_t> stage_off;
-  int64_t add(int64_t count, int64_t R, int64_t M, int64_t mul) {
-    TwSeg s{total, count, R, M, mul};
+  int64_t add(int64_t count, int64_t R, int64_t M, int64_t mul, bool rest = false) {
+    TwSeg s{total, count, R, M, mul, rest};
     segs.push_back(s);
     total += count;
     return s.off;
   }
-  // one segment per stage s >= 1 of the (L, P) schedule
+  // one segment per stage s >= 1 of the (L, P) schedule; beyond 4096 points
+  // also the rests of the last but one stage's entries (TwFac)
   int64_t add_stage_table(int L, int P) {
     auto key = std::make_pair(L, P);
     auto it = stage_off.find(key);
@@ -925,6 +926,7 @@ struct TableBuild {
       add((int64_t)ns * PP, PP, (int64_t)ns * PP, 1);
       ns *= PP;
     }
+    if (L > 4096 && S > 2) add(ns / PP, PP, ns / PP, 1, true);
     if (total == start) add(1, 0, 1, 0);  // one-stage transform: placeholder entry
     stage_off[key] = start;
     return start;
@@ -933,11 +935,7 @@ struct TableBuild {
 
 void host_fill(const std::vector<TwSeg>& segs, std::vector<float2>& tab) {
   for (const TwSeg& s : segs)
-    for (int64_t i = 0; i < s.count; ++i) {
-      double c, sn;
-      twiddle_fp64(seg_exponent(s, i), s.M, &c, &sn);
-      tab[s.off + i] = make_float2((float)c, (float)-sn);
-    }
+    for (int64_t i = 0; i < s.count; ++i) tab[s.off + i] = seg_value(s, i);
 }
 
 int upload_tables(fft_plan_s* p, TableBuild& tb, bool on_gpu) {
@@ -1230,10 +1228,12 @@ int fft_plan_ex(const int64_t* n, int64_t batch, int dims, int dtype, int direct
     const PassSpec& ps = S.passes[i];
     if (!ps.v) continue;
     if (ps.v->tw_split) {
-      // the two factor tables of W_L: W_L^i (i < 2^a), W_L^{i 2^a}
+      // the two factor tables of W_L: W_L^i (i < 2^a), W_L^{i 2^a}, and the
+      // rests of the second one
       const int lg = ilog2_64(ps.v->L), la = (lg + 1) / 2;
       stage_off[i] = tb.add((int64_t)1 << la, 0, ps.v->L, 1);
       tb.add((int64_t)1 << (lg - la), 0, ps.v->L, (int64_t)1 << la);
+      tb.add((int64_t)1 << (lg - la), 0, ps.v->L, (int64_t)1 << la, true);
     } else {
       stage_off[i] = tb.add_stage_table(ps.v->L, ps.v->P);
     }

@@ -33,11 +33,8 @@ __global__ void __launch_bounds__(256) k_twiddle_fp64(float2* table, const TwSeg
   if (g >= nseg) return;
   const TwSeg sg = segs[g];
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < sg.count;
-       i += (int64_t)gridDim.x * 256) {
-    double c, s;
-    twiddle_fp64(seg_exponent(sg, i), sg.M, &c, &s);
-    table[sg.off + i] = make_float2((float)c, (float)-s);
-  }
+       i += (int64_t)gridDim.x * 256)
+    table[sg.off + i] = seg_value(sg, i);
 }
 
 hipError_t launch_twiddle_fp64(float2* table, const TwSeg* d_segs, int nseg, int64_t max_count,

@@ -56,7 +56,8 @@ __global__ void __launch_bounds__((W * Sched<L, P>::T), 1) k_rowcol(PassArgs a) 
 
   int tid = threadIdx.x;
   if constexpr (TWP == 2) {
-    for (int i = tid; i < tw_split_entries(L); i += NT) twl[i] = a.tw[i];
+    constexpr int LO = 1 << ((ilog2(L) + 1) / 2);  // the factors of small angle
+    for (int i = tid; i < tw_split_entries(L); i += NT) twl[i] = i < LO ? tw_minus_one(a.tw[i]) : a.tw[i];
   } else {
     TwLds<L, P>::copy(twl, a.tw, tid, NT);
   }

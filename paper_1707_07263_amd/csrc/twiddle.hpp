@@ -18,8 +18,10 @@ namespace mfft {
 // Segment of a table: entries table[off + i], i < count, hold W_M^{e(i)} with
 //   e(i) = (i / R) * (i % R) * mul   if R > 0  (2-D table: row i / R, column i % R)
 //   e(i) = i * mul                   if R == 0 (linear table)
+// or, with `rest`, what their rounding to float32 left out of them.
 struct TwSeg {
   int64_t off, count, R, M, mul;
+  bool rest;
 };
 
 __host__ __device__ inline int64_t seg_exponent(const TwSeg& s, int64_t i) {
@@ -50,6 +52,14 @@ __host__ __device__ inline void twiddle_fp64(int64_t e, int64_t M, double* c_out
     case 2: *c_out = -cs; *s_out = -sn; break;
     default: *c_out = sn; *s_out = -cs; break;
   }
+}
+
+// Entry i of a segment.
+__host__ __device__ inline float2 seg_value(const TwSeg& s, int64_t i) {
+  double c, sn;
+  twiddle_fp64(seg_exponent(s, i), s.M, &c, &sn);
+  const float2 w = make_float2((float)c, (float)-sn);
+  return s.rest ? make_float2((float)(c - w.x), (float)(-sn - w.y)) : w;
 }
 
 hipError_t launch_twiddle_fp64(float2* table, const TwSeg* d_segs, int nseg, int64_t max_count,

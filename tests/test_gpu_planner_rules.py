@@ -140,3 +140,29 @@ def test_images_by_rule(dev, rows, cols, batch, inverse):
     z = xt.clone()
     plan.exec(z, z)
     assert torch.equal(z, got)
+
+
+# stage twiddles as products of two factors against the same butterflies with
+# the stage table: a product is rounded once at its own size, like a table's
+# entry, beside terms some 2^-3 of that, so the errors differ by about 1%
+@pytest.mark.parametrize("shape,factors,table", [
+    ([8192], "single=r8192p16w1q_c64", "single=r8192p16w1_c64"),
+    ([64, 4096], "rowcol=4;row=f4096p16w4q_c64", "rowcol=4;row=f4096p16w4qx_c64"),
+])
+def test_factored_twiddles_are_as_good_as_tables(dev, shape, factors, table):
+    n = int(np.prod(shape))
+    batch = (1 << 20) // n
+    x = workloads.normal_batch(n, batch, seed=5).reshape([batch] + shape).astype(np.complex64)
+    xt = to_gpu_c64(x, dev)
+    ref = (oracle.fft if len(shape) == 1 else oracle.fft2)(x)
+    err = []
+    for schedule in (factors, table):
+        y = torch.empty_like(xt)
+        h = capi.fft_plan_ex(shape, batch, len(shape), capi.FFT_C64, capi.FFT_FORWARD, schedule)
+        try:
+            capi.fft_exec(h, xt.data_ptr(), y.data_ptr(), torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+        finally:
+            capi.fft_destroy(h)
+        err.append(np.linalg.norm(y.cpu().numpy().ravel() - np.asarray(ref).ravel()))
+    assert err[0] <= 1.01 * err[1], err
