@@ -67,7 +67,8 @@ def _many_key(sizes, dtype):
 # 8192 rows), and the row pass takes 0 to 8 us more.  Per row length the fused
 # variants for r = 2 and 4.  Both passes together, 2^24 points: 2048 x 1024
 # 106 -> 93 us, 2048 x 4096 109 -> 96, 4096 x 512 144 -> 98, 4096 x 2048 142 -> 96,
-# 8192 x 1024 180 -> 109; 2^22 points: 31 -> 30, 35 -> 30, 45 -> 31.  r = 2 leaves
+# 8192 x 1024 180 -> 109 (since then 0 to 2 us more for the factors'
+# rests); 2^22 points: 31 -> 30, 35 -> 30, 45 -> 31.  r = 2 leaves
 # the row pass of long rows two workgroups per CU, but 2048-point columns of a
 # 4096-row image cost more than that gains (108 against 96).
 _FUSED_ROWS = {256: {4: "f256p8w4q_c64"}, 512: {4: "f512p8w4q_c64"}, 1024: {4: "f1024p16w4q_c64"},

@@ -112,13 +112,13 @@ size_t esize(int dtype) { return dtype == FFT_C64 ? 8 : 4; }
 //
 // Rows (contiguous lines): 8 points per lane and 256 lanes a workgroup, so
 // that 32 waves are resident per CU and one workgroup's loads overlap
-// another's butterflies (1024 points, complex64: 53 us against 69 with 16
-// points per lane and 512 lanes; fp16: 35 against 48).  Rows of 1024 to 4096
+// another's butterflies (1024 points, complex64: 52-56 us against 63-68 with 16
+// points per lane and 512 lanes; fp16: 34 against 45-49).  Rows of 1024 to 4096
 // complex64 points with at least 8 tiles per CU: persistent, the next tile in
-// flight (51-54 against 53-58 us; with 2 tiles per CU it is the other way
-// round, 12.5 against 10.4 us for 2^21 points).  Longer rows hold one line per
+// flight (51-54 against 52-56 us; with 2 tiles per CU it is the other way
+// round, 10.9 against 8.7 us for 2^21 points).  Longer rows hold one line per
 // workgroup; their stage twiddles come from factor tables in LDS and the next
-// line is in flight (16384: 82 us against 116).
+// line is in flight (16384: 69 us against 84 with a table, no line in flight).
 //
 // Columns and first passes of a split: as wide as LDS and registers allow
 // while there are tiles for every CU (two for every CU where a tile of 32

@@ -1057,8 +1057,8 @@ int blocks_many_2l() {
 // their loads, butterflies and stores overlap each other's; the last round of
 // a launch is a tile of 4096 points instead of 8192.  Measured against the
 // pipelined two-launch kernel, both with one N1 rule: 512 lengths 2^8 .. 2^16
-// (7.55 M points) complex64 63.2 -> 56.1 us, fp16 58.2 -> 41.1; 1000 lengths
-// 2^4 .. 2^13 fp16 25.1 -> 14.7; 300 lengths 2^8 .. 2^12 12.9 -> 7.5.  16 points
+// (6.92 M points) complex64 59.2 -> 47.8 us, fp16 54.7 -> 33.5; 1000 lengths
+// 2^4 .. 2^13 fp16 23.5 -> 10.8; 300 lengths 2^8 .. 2^12 12.5 -> 5.6.  16 points
 // per lane (256 lanes) ran 0 to 15% slower.
 // ---------------------------------------------------------------------------
 template <int L, int P, int NT, int KIND, typename TS>
