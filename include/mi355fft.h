@@ -124,7 +124,10 @@ int fft_plan(const int64_t *n, int64_t batch, int dims, int dtype, int direction
  *                                       in place, whose tiles can be r times
  *                                       wider.  'row=' then names a fused
  *                                       variant ('f'), 'col=' an M-point column
- *                                       variant.  In place needs a workspace.)
+ *                                       variant.  In place without a workspace
+ *                                       the rows are brought into the order
+ *                                       r*n1 + j first, one more pass over the
+ *                                       image; the same results)
  *             | 'method=' lds|levels  (1-D only.  'levels' is the method the
  *                                       paper replaces (Sec. 2.2, Fig. 2), kept
  *                                       for comparison: one radix-2 kernel per
@@ -259,9 +262,9 @@ int fft_many_set_wait_limit(fft_plan_t plan, int64_t microseconds);
  * Queue the transform on `stream`.  Asynchronous: no host synchronisation, no
  * allocation, no host reads of device data, so it may be captured into a
  * hipGraph.  `in` and `out` must not partially overlap; in == out is allowed
- * for one-pass plans, for three-pass plans, and for two-pass plans once a
- * workspace of fft_workspace_size() bytes is set (else FFT_ERR_INPLACE).  Input data are
- * not modified unless in == out.  A plan may be executed on several streams;
+ * for one-pass plans, for three-pass plans, for 2-D plans, and for 1-D two-pass
+ * plans once a workspace of fft_workspace_size() bytes is set (else
+ * FFT_ERR_INPLACE).  Input data are not modified unless in == out.  A plan may be executed on several streams;
  * execs that share a workspace (in-place two-pass, three-pass and batched
  * plans) must not overlap in time, and calls on one plan from several host
  * threads must be serialised by the caller (the plan's timing state is not
@@ -270,10 +273,18 @@ int fft_many_set_wait_limit(fft_plan_t plan, int64_t microseconds);
 int fft_exec(fft_plan_t plan, const void *in, void *out, void *stream);
 
 /*
+ * As fft_exec, with `ws`, device memory of `bytes` bytes (at least
+ * fft_workspace_size()), as the workspace of this exec only, so that execs of
+ * one plan on several streams can each bring their own.  The plan's own
+ * workspace, if any, is neither used nor changed.
+ */
+int fft_exec_ws(fft_plan_t plan, const void *in, void *out, void *stream, void *ws, size_t bytes);
+
+/*
  * For callers that cannot allocate device memory (code under stream capture,
  * tight serving loops, harnesses that forbid hipMalloc).
  * As fft_exec, except that the scratch an exec needs -- a batched plan's
- * queue and completion counters, the intermediate of an in-place two-pass
+ * queue and completion counters, the intermediate of an in-place 1-D two-pass
  * exec, or the intermediate of a three-pass plan -- is taken from one static
  * device array of FFT_STATIC_SCRATCH_BYTES (32 MiB) that the library holds on
  * every device it runs on until the process ends, instead of the plan's
@@ -308,7 +319,8 @@ int fft_set_scale(fft_plan_t plan, double scale);
 
 /*
  * Workspace for the global-memory exchanges between passes (Sec. 2.3.2/2.3.3).
- * Device scratch a plan needs to run in place (1-D two-pass), on every exec
+ * Device scratch a plan needs to run in place (1-D two-pass; 2-D with
+ * 'rowcol=': optional, it saves the pass that orders the rows), on every exec
  * (1-D three-pass plans, lengths above 2^24: one buffer of batch * N
  * elements, allocated by the plan) or, for plan_many, for its queue and
  * counters.  fft_set_workspace hands the plan caller-owned device memory of

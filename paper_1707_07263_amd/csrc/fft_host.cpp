@@ -275,7 +275,9 @@ struct PassSpec {
   int64_t tw_rows = 0;         // rows of its step table
   int64_t colr_N = 0;          // fused row pass: its column twiddles W_R^e, e < colr_N (0: none)
   int64_t scale_len = 0;       // transform length this pass accounts for (0: the variant's L)
-  std::vector<int32_t> line_map;  // row pass of the three-pass 2-D plan
+  // row pass of the three-pass 2-D plan: its rows in order; fused row pass:
+  // the first row of each cycle of the row shuffle
+  std::vector<int32_t> line_map;
   // launched once per transform of the batch, pointers advanced by the
   // transform's length (the last pass of the three-pass 1-D plan)
   bool per_transform = false;
@@ -286,6 +288,9 @@ struct Schedule {
   int64_t split[2] = {0, 0};
   int64_t points = 0;
   bool inplace_needs_ws = false;
+  // in place without a workspace the rows are shuffled first, and the fused
+  // row pass then writes the rows that it reads
+  bool row_shuffle = false;
   // every exec needs a workspace of `points` elements (passes read or write
   // SEL_WS); the plan allocates one unless the caller sets its own
   bool always_ws = false;
@@ -566,6 +571,20 @@ int build_three_pass_2d(int64_t R, int64_t C, int64_t batch, int dtype, const Ov
   return FFT_OK;
 }
 
+// The smallest row of each cycle of p -> p rotated left by lg_r in lg_rows
+// bits, but for rows that stay where they are.
+std::vector<int32_t> shuffle_cycles(int lg_rows, int lg_r) {
+  const int32_t mask = ((int32_t)1 << lg_rows) - 1;
+  std::vector<int32_t> starts;
+  for (int32_t p = 0; p <= mask; ++p) {
+    int32_t q = p;
+    do q = ((q << lg_r) | (q >> (lg_rows - lg_r))) & mask;
+    while (q > p);
+    if (q == p && ((p << lg_r | p >> (lg_rows - lg_r)) & mask) != p) starts.push_back(p);
+  }
+  return starts;
+}
+
 int build_schedule_inner(const int64_t* n, int64_t batch, int dims, int dtype, const Overrides& ov,
                          Schedule* out) {
   Schedule S;
@@ -695,7 +714,8 @@ int build_schedule_inner(const int64_t* n, int64_t batch, int dims, int dtype, c
       PassArgs& a = f.args;
       a.in_batch = a.out_batch = R * C;
       a.in_line = a.out_line = C;
-      a.in_elem = a.out_elem = 1;
+      a.in_elem = M * C;
+      a.out_elem = 1;
       a.lines = (int32_t)R;
       a.tiles_per_batch = (int32_t)M;
       a.total_tiles = M * batch;
@@ -719,6 +739,8 @@ int build_schedule_inner(const int64_t* n, int64_t batch, int dims, int dtype, c
       cl.dst = SEL_OUT;
       cl.last = true;
       S.inplace_needs_ws = true;
+      S.row_shuffle = true;
+      f.line_map = shuffle_cycles(lgR, ilog2_64(r));
       S.passes.push_back(f);
       S.passes.push_back(cl);
       *out = S;
@@ -1377,12 +1399,13 @@ namespace {
 
 // Bytes of workspace one exec of `p` with these buffers reads or writes (0:
 // none): the batched plan's queue state, the in-place two-pass intermediate,
-// or the three-pass intermediate.
+// or the three-pass intermediate.  The fused 2-D plan does without.
 size_t exec_scratch_bytes(const fft_plan_s* p, const void* in, const void* out) {
   if (p->kind == 1) return many_workspace_bytes(p->many);
   if (p->kind != 0) return 0;
   const Schedule& S = p->sched;
-  const bool ws = S.always_ws || (in == out && S.passes.size() > 1 && S.inplace_needs_ws);
+  const bool ws =
+      S.always_ws || (in == out && S.passes.size() > 1 && S.inplace_needs_ws && !S.row_shuffle);
   return ws ? (size_t)S.points * esize(p->dtype) : 0;
 }
 
@@ -1393,12 +1416,13 @@ __global__ void k_zero_words(uint32_t* p, int64_t n) {
 
 // fft_exec with the plan's workspace replaced by `ws_over` when it is not
 // NULL (the caller has checked its size); a batched plan's queue state there
-// is cleared by a fill kernel first.
-int exec_impl(fft_plan_t p, const void* in, void* out, void* stream, void* ws_over) {
+// is cleared by a fill kernel first.  own_ws false: the plan's workspace is
+// left alone.
+int exec_impl(fft_plan_t p, const void* in, void* out, void* stream, void* ws_over, bool own_ws = true) {
   if (!p || !in || !out) return FFT_ERR_INVALID_ARGUMENT;
   if (check_ptr(in, p->dtype) || check_ptr(out, p->dtype)) return FFT_ERR_ALIGNMENT;
   hipStream_t s = (hipStream_t)stream;
-  void* const plan_ws = ws_over ? ws_over : p->ws;
+  void* const plan_ws = ws_over ? ws_over : own_ws ? p->ws : nullptr;
   if (p->kind == 1) {
     const size_t mbytes = (size_t)p->many.points * esize(p->dtype);
     const char* mi = (const char*)in;
@@ -1468,9 +1492,10 @@ int exec_impl(fft_plan_t p, const void* in, void* out, void* stream, void* ws_ov
   }
   void* ws = nullptr;
   if (same && S.passes.size() > 1 && S.inplace_needs_ws) {
-    if (!plan_ws) return FFT_ERR_INPLACE;
+    if (!plan_ws && !S.row_shuffle) return FFT_ERR_INPLACE;
     ws = plan_ws;
   }
+  const bool shuffled = same && S.row_shuffle && !ws;
   if (S.always_ws && !plan_ws) return FFT_ERR_INPLACE;
   const bool inv = p->direction > 0;
   hipEvent_t* slot = prof_slot(p, s);
@@ -1489,10 +1514,16 @@ int exec_impl(fft_plan_t p, const void* in, void* out, void* stream, void* ws_ov
       dst = ws ? (i == 0 ? ws : out) : out;
     }
     // a single kernel launch takes the events itself (its own start and end
-    // times); a copy or a per-transform loop is bracketed by markers
-    const bool one_launch = ps.v && !(ps.per_transform && p->batch > 1);
+    // times); a copy, a per-transform loop or a shuffle and its pass are
+    // bracketed by markers
+    const bool shuffle = shuffled && i == 0;
+    const bool one_launch = ps.v && !(ps.per_transform && p->batch > 1) && !shuffle;
     if (slot && !one_launch) hipEventRecord(slot[2 * i], s);
-    hipError_t e;
+    hipError_t e = hipSuccess;
+    if (shuffle)
+      e = launch_row_shuffle(out, ps.args.line_map, (int)ps.line_map.size(), ilog2_64(p->n[0]),
+                             ilog2_64(ps.v->W), (int)p->n[1], p->batch, s);
+    if (e != hipSuccess) return hip_fail(e);
     if (!ps.v) {
       e = launch_scale_copy(p->dtype, src, dst, ps.copy_n, (float)p->scale, s);
     } else {
@@ -1506,6 +1537,10 @@ int exec_impl(fft_plan_t p, const void* in, void* out, void* stream, void* ws_ov
                               : (inv ? 1.0f / (float)(ps.scale_len ? ps.scale_len : ps.v->L) : 1.0f);
       a.conj_in = (inv && ps.first) ? 1 : 0;
       a.conj_out = (inv && ps.last) ? 1 : 0;
+      if (shuffle) {
+        a.in_line = ps.v->W * p->n[1];
+        a.in_elem = p->n[1];
+      }
       if (ps.per_transform && p->batch > 1) {
         const size_t step = (size_t)(S.points / p->batch) * esize(p->dtype);
         e = hipSuccess;
@@ -1515,7 +1550,8 @@ int exec_impl(fft_plan_t p, const void* in, void* out, void* stream, void* ws_ov
           e = ps.v->launch(a, s, nullptr, nullptr);
         }
       } else {
-        e = ps.v->launch(a, s, slot ? slot[2 * i] : nullptr, slot ? slot[2 * i + 1] : nullptr);
+        hipEvent_t* own = one_launch ? slot : nullptr;
+        e = ps.v->launch(a, s, own ? own[2 * i] : nullptr, own ? own[2 * i + 1] : nullptr);
       }
     }
     if (slot && !one_launch) hipEventRecord(slot[2 * i + 1], s);
@@ -1560,10 +1596,19 @@ int fft_exec(fft_plan_t p, const void* in, void* out, void* stream) {
   return exec_impl(p, in, out, stream, nullptr);
 }
 
+int fft_exec_ws(fft_plan_t p, const void* in, void* out, void* stream, void* ws, size_t bytes) {
+  if (!p || !ws) return FFT_ERR_INVALID_ARGUMENT;
+  size_t need = 0;
+  fft_workspace_size(p, &need);
+  if (bytes < need) return FFT_ERR_INVALID_ARGUMENT;
+  if ((uintptr_t)ws % 16) return FFT_ERR_ALIGNMENT;
+  return exec_impl(p, in, out, stream, ws);
+}
+
 int fft_exec_static(fft_plan_t p, const void* in, void* out, void* stream) {
   if (!p || !in || !out) return FFT_ERR_INVALID_ARGUMENT;
   const size_t need = exec_scratch_bytes(p, in, out);
-  if (need == 0) return exec_impl(p, in, out, stream, nullptr);
+  if (need == 0) return exec_impl(p, in, out, stream, nullptr, !p->sched.row_shuffle);
   if (need > (size_t)FFT_STATIC_SCRATCH_BYTES) return FFT_ERR_SCRATCH_LIMIT;
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);

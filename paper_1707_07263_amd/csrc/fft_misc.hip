@@ -1,5 +1,8 @@
-// Small kernels: copy-scale for length-1 transforms, and FP64 twiddle-table
-// generation on the GPU (used for 1-D lengths >= 2^22).
+// Small kernels: copy-scale for length-1 transforms, the row shuffle of the
+// fused 2-D plan in place, and FP64 twiddle-table generation on the GPU (used
+// for 1-D lengths >= 2^22).
+#include <algorithm>
+
 #include "twiddle.hpp"
 #include "variants.hpp"
 
@@ -23,6 +26,49 @@ hipError_t launch_scale_copy(int dtype, const void* in, void* out, int64_t n, fl
                          (const c16bf*)in, (c16bf*)out, n, scale);
       break;
   }
+  return hipGetLastError();
+}
+
+// Images of R = 2^lg_rows rows of C points, in place: row n1 + (R/r)*j moves to
+// row r*n1 + j, where the fused row pass writes it (k_rowcol), so that this
+// pass then needs no second buffer.  That is a rotation of the row number's
+// bits by log2 r, whose cycles have at most lg_rows rows: a lane holds one
+// column of a whole cycle in registers, so no two lanes share an element.
+// Workgroup: 256 columns of the cycle that starts at row starts[blockIdx.y].
+// Bound by the copy it is.
+constexpr int kMaxCycle = 14;
+__global__ void __launch_bounds__(256) k_row_shuffle(float2* x, const int32_t* __restrict__ starts, int lg_rows,
+                                                     int lg_r, int C, int64_t batch) {
+  const uint32_t first = starts[blockIdx.y], mask = (1u << lg_rows) - 1;
+  auto next = [&](uint32_t p) { return ((p << lg_r) | (p >> (lg_rows - lg_r))) & mask; };
+  int len = 1;
+  for (uint32_t p = next(first); p != first; p = next(p)) ++len;
+  const int c = blockIdx.x * 256 + threadIdx.x;
+  if (c >= C) return;
+  for (int64_t b = blockIdx.z; b < batch; b += gridDim.z) {
+    float2* img = x + b * ((int64_t)C << lg_rows) + c;
+    float2 v[kMaxCycle];
+    uint32_t p = first;
+#pragma unroll
+    for (int i = 0; i < kMaxCycle; ++i)
+      if (i < len) {
+        v[i] = img[(int64_t)p * C];
+        p = next(p);
+      }
+#pragma unroll
+    for (int i = 0; i < kMaxCycle; ++i)
+      if (i < len) {
+        p = next(p);  // the cycle closes: row `first` again, then the rest
+        img[(int64_t)p * C] = v[i];
+      }
+  }
+}
+
+hipError_t launch_row_shuffle(void* x, const int32_t* starts, int cycles, int lg_rows, int lg_r, int C, int64_t batch,
+                              hipStream_t s) {
+  if (lg_rows > kMaxCycle || lg_r >= lg_rows) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_row_shuffle, dim3((C + 255) / 256, (unsigned)cycles, (unsigned)std::min<int64_t>(batch, 65535)),
+                     dim3(256), 0, s, (float2*)x, starts, lg_rows, lg_r, C, batch);
   return hipGetLastError();
 }
 

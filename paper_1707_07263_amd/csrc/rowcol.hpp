@@ -34,11 +34,14 @@ __host__ __device__ constexpr int rowcol_lds_entries() {
 }
 
 // PassArgs as used here: lines = R rows per image, tiles_per_batch = M =
-// R / W (a power of two, tw_shift = log2 M), in_line = out_line = C,
-// in_elem = out_elem = 1, in_batch = out_batch = R * C, tw = the row length's
+// R / W (a power of two, tw_shift = log2 M), in_line and in_elem the strides
+// of n1 and of j in the input (C and M*C; after k_row_shuffle W*C and C),
+// out_line = C, out_elem = 1, in_batch = out_batch = R * C, tw = the row length's
 // stage table (TWP 1) or the factor tables of W_L (TWP 2), tw_lo = W_R^e
 // for e < R.  Persistent: workgroup g walks tiles g, g + G, ... with the
-// next tile's loads in flight.
+// next tile's loads in flight.  After k_row_shuffle in may be out: a tile then
+// writes the rows that it read, and every wave's reads are done before the
+// exchange's first barrier.
 template <int L, int P, int W, int EX, int TWP, typename TS>
 __global__ void __launch_bounds__((W * Sched<L, P>::T), 1) k_rowcol(PassArgs a) {
   using S = Sched<L, P>;
@@ -74,15 +77,13 @@ __global__ void __launch_bounds__((W * Sched<L, P>::T), 1) k_rowcol(PassArgs a) 
     const int64_t b = tl >> lgM;
     const int64_t n1 = tl & (M - 1);
     const int m = tid / T, t = tid % T;
-    const TS* src = reinterpret_cast<const TS*>(a.in) + b * a.in_batch + (n1 + m * M) * a.in_line +
-                    (int64_t)t * a.in_elem;
-    const int64_t step = (int64_t)T * a.in_elem;
+    const TS* src = reinterpret_cast<const TS*>(a.in) + b * a.in_batch + n1 * a.in_line + m * a.in_elem + t;
 #pragma unroll
     for (int q = 0; q < PP; ++q) {
       if constexpr (sizeof(TS) == 8)
-        vn[q] = load_stream(reinterpret_cast<const float2*>(src + q * step));
+        vn[q] = load_stream(reinterpret_cast<const float2*>(src + q * T));
       else
-        vn[q] = src[q * step];
+        vn[q] = src[q * T];
     }
     // W_R^{n1 k2}, k2 < W (n1 k2 < M W = R)
 #pragma unroll

@@ -145,4 +145,9 @@ void add_variants_c64_rowcol(void (*add)(const Variant&));
 hipError_t launch_scale_copy(int dtype, const void* in, void* out, int64_t n, float scale,
                              hipStream_t s);
 
+// Rows of `batch` complex64 images to the order the fused row pass writes, in
+// place; `starts` holds one row of each cycle (2^lg_rows rows, at most 2^14)
+hipError_t launch_row_shuffle(void* x, const int32_t* starts, int cycles, int lg_rows, int lg_r, int C, int64_t batch,
+                              hipStream_t s);
+
 }  // namespace mfft
