@@ -15,6 +15,8 @@
 #include <type_traits>
 #include <stdint.h>
 
+#include "twiddle.hpp"
+
 namespace mfft {
 
 // ---------------------------------------------------------------------------
@@ -33,10 +35,16 @@ __device__ __forceinline__ float2 mul_negi(float2 a) { return make_float2(a.y, -
 // x * W_64^e with W_64 = exp(-2*pi*i/64), e a compile-time constant after
 // unrolling (0 <= e < 64).  Exact forms for multiples of pi/4; otherwise the
 // cosine comes from a quarter-wave table of cos(2*pi*k/64), k = 0..16.
+// BAL: cos(pi/16) and cos(pi/8) are the float32 above.  All the constants of a
+// 32-point butterfly round down, sqrt(1/2) too, so that every product loses
+// some 2e-8 of its size in the same direction and the whole transform a third
+// of its error; with these two rounded up the losses cancel (twiddle.hpp has
+// the stage tables' part).
+template <bool BAL = false>
 __device__ __forceinline__ float2 mul_w64(float2 x, int e) {
   constexpr float Q[17] = {
-      1.0f,                        0.995184726672196886244837f, 0.980785280403230449126182f,
-      0.956940335732208864935798f, 0.923879532511286756128183f, 0.881921264348355029712757f,
+      1.0f,                        0.995184726672196886244837f, BAL ? kCosPi16Up : 0.980785280403230449126182f,
+      0.956940335732208864935798f, BAL ? kCosPi8Up : 0.923879532511286756128183f, 0.881921264348355029712757f,
       0.831469612302545237078788f, 0.773010453362736960810907f, 0.707106781186547524400844f,
       0.634393284163645498215172f, 0.555570233019602224742831f, 0.471396736825997648556388f,
       0.382683432365089771728460f, 0.290284677254462367636192f, 0.195090322016128267848285f,
@@ -57,6 +65,22 @@ __device__ __forceinline__ float2 mul_w64(float2 x, int e) {
   else if (e < 48) { c = -Q[e - 32]; s = -Q[48 - e]; }
   else { c = Q[64 - e]; s = -Q[e - 48]; }
   return make_float2(x.x * c + x.y * s, x.y * c - x.x * s);
+}
+
+// x * W_16^r, r a compile-time constant after unrolling (0 < r < 8), each
+// constant with what its rounding left; the rests are positive, so that an
+// infinity times a constant stays one.
+__device__ __forceinline__ float2 mul_w16_rest(float2 x, int r) {
+  constexpr double D[5] = {1.0, 0.923879532511286756128183, 0.707106781186547524400844,
+                           0.382683432365089771728460, 0.0};
+  constexpr float H[5] = {1.0f, (float)D[1], (float)D[2], (float)D[3], 0.0f};
+  constexpr float E[5] = {0.0f, (float)(D[1] - H[1]), (float)(D[2] - H[2]), (float)(D[3] - H[3]), 0.0f};
+  static_assert(E[1] > 0 && E[2] > 0 && E[3] > 0, "rests are positive");
+  if (r == 4) return make_float2(x.y, -x.x);
+  const int ic = r < 4 ? r : 8 - r, is = r < 4 ? 4 - r : r - 4;  // |cos|, sin of 2 pi r/16
+  const float2 u = r < 4 ? x : make_float2(-x.x, -x.y);          // cos < 0 beyond a quarter
+  return make_float2(fmaf(u.x, H[ic], fmaf(x.y, H[is], fmaf(u.x, E[ic], x.y * E[is]))),
+                     fmaf(u.y, H[ic], fmaf(-x.x, H[is], fmaf(u.y, E[ic], -x.x * E[is]))));
 }
 
 // ---------------------------------------------------------------------------
@@ -89,7 +113,7 @@ template <> struct Dft<4> {
 };
 
 // R = R1 * R2: n = R2*n1 + n2, k = k1 + R1*k2.
-template <int R1, int R2> struct DftSplit {
+template <int R1, int R2, bool BAL = false> struct DftSplit {
   static constexpr int R = R1 * R2;
   __device__ __forceinline__ static void run(float2* a) {
     float2 y[R];
@@ -100,7 +124,7 @@ template <int R1, int R2> struct DftSplit {
       for (int n1 = 0; n1 < R1; ++n1) s[n1] = a[R2 * n1 + n2];
       Dft<R1>::run(s);
 #pragma unroll
-      for (int k1 = 0; k1 < R1; ++k1) y[k1 * R2 + n2] = mul_w64(s[k1], (n2 * k1 * (64 / R)) & 63);
+      for (int k1 = 0; k1 < R1; ++k1) y[k1 * R2 + n2] = mul_w64<BAL>(s[k1], (n2 * k1 * (64 / R)) & 63);
     }
 #pragma unroll
     for (int k1 = 0; k1 < R1; ++k1) {
@@ -117,7 +141,7 @@ template <> struct Dft<16> {
   __device__ __forceinline__ static void run(float2* a) { DftSplit<4, 4>::run(a); }
 };
 template <> struct Dft<32> {
-  __device__ __forceinline__ static void run(float2* a) { DftSplit<4, 8>::run(a); }
+  __device__ __forceinline__ static void run(float2* a) { DftSplit<4, 8, true>::run(a); }
 };
 
 // ---------------------------------------------------------------------------
@@ -517,7 +541,11 @@ __device__ __forceinline__ void exchange(float2* v, void* ldsv, int m, int m2, i
 // registers that two workgroups per CU allow.
 template <int L, int P, int s, int TWP> struct StageTw {
   using S = Sched<L, P>;
-  static constexpr bool AHEAD = TWP == 0 && s > 0 && s < S::S && S::PP <= 16;
+  // 16 points by 8: the second stage's factors are 1 or W_16^r.  As constants
+  // with their rests they make the two stages no less accurate than one
+  // 16-point butterfly (6.10e-8 of the result; with rounded factors 6.37e-8)
+  static constexpr bool CONST16 = L == 16 && S::PP == 8 && s == 1;
+  static constexpr bool AHEAD = TWP == 0 && s > 0 && s < S::S && S::PP <= 16 && !CONST16;
   static constexpr int N = AHEAD ? S::PP : 1;
   float2 w[N];
   // for the lane that holds points t + q*T in stage s
@@ -556,7 +584,13 @@ struct Stage {
       float2 x[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) x[r] = v[b + r * NB];
-      if constexpr (TW::AHEAD) {
+      if constexpr (TW::CONST16) {
+#pragma unroll
+        for (int r = 1; r < R; ++r) {
+          const float2 y = mul_w16_rest(x[r], r);
+          x[r] = k ? y : x[r];
+        }
+      } else if constexpr (TW::AHEAD) {
 #pragma unroll
         for (int r = 1; r < R; ++r) x[r] = cmul(x[r], ahead.w[b * R + r]);
       } else if constexpr (s > 0 && TWP == 2) {

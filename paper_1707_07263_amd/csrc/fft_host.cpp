@@ -926,8 +926,8 @@ struct TableBuild {
   std::vector<TwSeg> segs;
   int64_t total = 0;
   std::map<std::pair<int, int>, int64_t> stage_off;
-  int64_t add(int64_t count, int64_t R, int64_t M, int64_t mul, bool rest = false) {
-    TwSeg s{total, count, R, M, mul, rest};
+  int64_t add(int64_t count, int64_t R, int64_t M, int64_t mul, bool rest = false, bool balanced = false) {
+    TwSeg s{total, count, R, M, mul, rest, balanced};
     segs.push_back(s);
     total += count;
     return s.off;
@@ -945,10 +945,10 @@ struct TableBuild {
     const int64_t start = total;
     int ns = FIRST;
     for (int s = 1; s < S; ++s) {
-      add((int64_t)ns * PP, PP, (int64_t)ns * PP, 1);
+      add((int64_t)ns * PP, PP, (int64_t)ns * PP, 1, false, true);
       ns *= PP;
     }
-    if (L > 4096 && S > 2) add(ns / PP, PP, ns / PP, 1, true);
+    if (L > 4096 && S > 2) add(ns / PP, PP, ns / PP, 1, true, true);
     if (total == start) add(1, 0, 1, 0);  // one-stage transform: placeholder entry
     stage_off[key] = start;
     return start;
@@ -1254,8 +1254,8 @@ int fft_plan_ex(const int64_t* n, int64_t batch, int dims, int dtype, int direct
       // rests of the second one
       const int lg = ilog2_64(ps.v->L), la = (lg + 1) / 2;
       stage_off[i] = tb.add((int64_t)1 << la, 0, ps.v->L, 1);
-      tb.add((int64_t)1 << (lg - la), 0, ps.v->L, (int64_t)1 << la);
-      tb.add((int64_t)1 << (lg - la), 0, ps.v->L, (int64_t)1 << la, true);
+      tb.add((int64_t)1 << (lg - la), 0, ps.v->L, (int64_t)1 << la, false, true);
+      tb.add((int64_t)1 << (lg - la), 0, ps.v->L, (int64_t)1 << la, true, true);
     } else {
       stage_off[i] = tb.add_stage_table(ps.v->L, ps.v->P);
     }
