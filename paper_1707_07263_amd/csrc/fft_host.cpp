@@ -138,6 +138,7 @@ struct Pref {
   int64_t min_tiles;
 };
 constexpr int64_t kCus = 256;  // MI355X
+constexpr int64_t kMaxLanes = UINT32_MAX;  // of one launch
 constexpr Pref kPrefs[] = {
     {ROLE_ROW, 32, 16, 8, 128, 0, 0, 0},
     {ROLE_ROW, 32, 32, 8, 64, 0, 0, 0},
@@ -254,8 +255,12 @@ const Variant* preferred(int role, int L, int dtype, int want_w, int64_t lines, 
     if ((lines + f.W - 1) / f.W * batches < f.min_tiles) continue;
     for (const Variant& v : variants())
       if (v.role == role && v.L == L && v.dtype == dtype && v.P == std::min(f.P, L) && v.W == f.W &&
-          v.persistent == f.persistent && v.ex == f.ex)
+          v.persistent == f.persistent && v.ex == f.ex) {
+        // 8 points per lane are too few from 2^35 points on (128 GiB in
+        // 16-bit storage): the general choice has 16
+        if (!v.persistent && (lines + v.W - 1) / v.W * batches > kMaxLanes / v.threads) break;
         return &v;
+      }
   }
   return pick(role, L, dtype, want_w, lines);
 }
@@ -514,6 +519,8 @@ int build_three_pass_2d(int64_t R, int64_t C, int64_t batch, int dtype, const Ov
   if (rc) return rc;
   rc = choose(ov.row, ROLE_ROW, (int)C, dtype, 2, R, 0, &rw.v);
   if (rc) return rc;
+  if (ov.row.empty() && !rw.v->persistent && R * batch / rw.v->W > kMaxLanes / rw.v->threads)
+    rw.v = pick(ROLE_ROW, (int)C, dtype, 64, R);
   // row tiles of an even number of rows never split a transpose pair (the
   // map lists the pairs first, then the diagonal rows), and whole tiles
   // cover the R rows of an image
@@ -1960,6 +1967,16 @@ int build_many(const int64_t* sizes, int64_t count, int dtype, int direction, co
   while (b_next < split_ids.size()) push_b(split_ids[b_next++]);
   if (items.size() > (size_t)INT32_MAX / 2) return FFT_ERR_UNSUPPORTED_SIZE;
   if (opt.pipe >= 2) split_launches(mb);
+  if (opt.pipe == 3 && std::max(mb->q_off[1], mb->q_off[2] - mb->q_off[1]) > kMaxLanes / opt.threads) {
+    // more tiles than one launch takes (2^35 points and more): the persistent
+    // kernel, whose grid does not grow with them
+    if (opt.flat) return FFT_ERR_UNSUPPORTED_SIZE;
+    ManyBuild queue;
+    const std::string s = (schedule && *schedule ? std::string(schedule) + ";" : std::string()) + "pipe=2";
+    const int rc = build_many(sizes, count, dtype, direction, s.c_str(), &queue);
+    if (!rc) *mb = std::move(queue);
+    return rc;
+  }
   return FFT_OK;
 }
 
