@@ -46,6 +46,8 @@ class Plan:
 
     def exec(self, x: torch.Tensor, out: torch.Tensor, stream: int | None = None) -> None:
         if stream is None:
+            if not x.is_cuda:
+                raise ValueError("input must be a GPU tensor where no stream is given")
             stream = _raw_stream(x.device.index)
             if self.optional_scratch and self.workspace is None and x.data_ptr() == out.data_ptr():
                 scratch = _scratch(self.optional_scratch, x.device)
@@ -90,9 +92,10 @@ def _scratch(nbytes: int, device):
 _cache: dict = {}
 _lock = threading.Lock()
 
-# the current stream's handle without building a torch.cuda.Stream (0.1 us
-# against 1.9)
-_raw_stream = torch._C._cuda_getCurrentRawStream
+# the current stream's handle of a device by index: without building a
+# torch.cuda.Stream where this torch has the function for it (0.1 us against 1.9)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+    lambda index: torch.cuda.current_stream(index).cuda_stream)
 
 # Plans by call signature: a repeated call finds its plan with one lookup,
 # where checking the shape, looking the tuned schedule up and building the
