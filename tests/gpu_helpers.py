@@ -55,3 +55,13 @@ def quantised(x, dt):
     pair = np.stack([np.asarray(x).real, np.asarray(x).imag], axis=-1).astype(np.float32)
     t = torch.from_numpy(pair).to(dt).float().numpy().astype(np.float64)
     return t[..., 0] + 1j * t[..., 1]
+
+
+def norms(t):
+    """2-norm of each row of a [rows, n] complex tensor on the GPU, as a host
+    tensor: squares summed in short pieces there and the pieces here.  A torch
+    sum or norm over rows of 2^19 points, which takes several workgroups per
+    row, was wrong twice in some hundred calls; the rows themselves were right."""
+    t = torch.view_as_real(t)
+    piece = math.gcd(t.shape[1] * 2, 1024)
+    return t.square().reshape(t.shape[0], -1, piece).sum(dim=2).cpu().sum(dim=1).sqrt()

@@ -1,0 +1,31 @@
+"""The cases of test_gpu_planner_variants reach every variant that the planner
+picks by itself (host only)."""
+import pytest
+
+import planner_cases
+from paper_1707_07263_amd import capi
+
+
+@pytest.mark.parametrize("dt", sorted(planner_cases.DTYPES))
+def test_every_default_variant_has_a_case(dt):
+    dtype = planner_cases.DTYPES[dt]
+    cases = planner_cases.lines(dtype) + planner_cases.images(dtype)
+    tested = {n for shape, batch in cases for n in planner_cases.plan_names(shape, batch, dtype)}
+    for lg in range(1, 25):
+        last = planner_cases.MAX_POINTS >> lg
+        for batch in {*range(1, min(last, 130) + 1), *(last * k // 97 for k in range(1, 98))} - {0}:
+            names = planner_cases.plan_names((1 << lg,), batch, dtype)
+            assert tested.issuperset(names), (lg, batch, names)
+    for lg_r in range(1, 14):
+        for lg_c in range(1, 14):
+            last = max(1, planner_cases.MAX_POINTS >> (lg_r + lg_c))
+            for batch in {1, 2, 3, 5, 17, 100, last // 3, last // 2, last} & set(range(1, last + 1)):
+                if batch << (lg_r + lg_c) <= planner_cases.MAX_POINTS:
+                    names = planner_cases.plan_names((1 << lg_r, 1 << lg_c), batch, dtype)
+                    assert tested.issuperset(names), (lg_r, lg_c, batch, names)
+
+
+def test_the_cases_are_the_steps():
+    # 1024-point rows in complex64 turn persistent at 2048 tiles of 4 rows
+    assert ((1024,), 8188) in planner_cases.lines(capi.FFT_C64)
+    assert ((1024,), 8189) in planner_cases.lines(capi.FFT_C64)
