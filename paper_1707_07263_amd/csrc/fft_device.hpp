@@ -667,14 +667,6 @@ __device__ __forceinline__ void run_stages(float2* v, void* lds, int& m, int& t,
 // the point index fastest (contiguous lines).  With TWID the outputs are
 // multiplied by W_N^{line*k} (the inter-pass twiddle of the N1 x N2 split).
 // ---------------------------------------------------------------------------
-// Waves per SIMD the kernel must allow so that every workgroup its LDS
-// footprint lets onto a CU can be resident (4 SIMDs per CU, at most 8 waves
-// per SIMD, 160 KB of LDS per CU); passed to the register allocator, capped
-// at 4 waves (128 VGPRs) so that no variant is squeezed into spilling.
-// Only row passes (contiguous lines in and out) take a line map; for the
-// other lane mappings the persistent pass knows it is absent at compile
-// time, so its loop carries no load whose result the next tile's addresses
-// would wait for.
 // What a strip pass stores for an output: with the inter-pass twiddle
 // (tw_base * tw_row, tw_base already times the pass's scale: a twiddled pass
 // is never the last, so its scale is a power of two and the product exact, and
@@ -686,6 +678,10 @@ __device__ __forceinline__ float2 out_value(float2 v, float2 tw_base, float2 tw_
   return make_float2(v.x * scale, v.y * scale_im);
 }
 
+// Only row passes (contiguous lines in and out) take a line map; for the
+// other lane mappings the persistent pass knows it is absent at compile
+// time, so its loop carries no load whose result the next tile's addresses
+// would wait for.
 template <int LOADM, int STOREM>
 __host__ __device__ constexpr bool kLineMap() {
   return LOADM == 0 && STOREM == 0;
@@ -706,6 +702,10 @@ __host__ __device__ constexpr bool kStagedRows() {
   return LOADM == 0 && STOREM == 0 && EX == 0 && T <= 8;
 }
 
+// Waves per SIMD the kernel must allow so that every workgroup its LDS
+// footprint lets onto a CU can be resident (4 SIMDs per CU, at most 8 waves
+// per SIMD, 160 KB of LDS per CU); passed to the register allocator, capped
+// at 4 waves (128 VGPRs) so that no variant is squeezed into spilling.
 template <int L, int P, int W, int EX>
 __host__ __device__ constexpr int strip_min_waves() {
   constexpr int nt = W * Sched<L, P>::T;

@@ -115,8 +115,12 @@ size_t esize(int dtype) { return dtype == FFT_C64 ? 8 : 4; }
 // another's butterflies (1024 points, complex64: 52-56 us against 63-68 with 16
 // points per lane and 512 lanes; fp16: 34 against 45-49).  Rows of 1024 to 4096
 // complex64 points with at least 8 tiles per CU: persistent, the next tile in
-// flight (51-54 against 52-56 us; with 2 tiles per CU it is the other way
-// round, 10.9 against 8.7 us for 2^21 points).  Longer rows hold one line per
+// flight (2^23 points 27.3 against 28.8 us; with 2 tiles per CU it is the other
+// way round, 10.9 against 8.7 us for 2^21 points), for 1024 and 2048 points up to
+// 1.5 * 2^24 in all: beyond, on buffers that the last-level cache does not hold,
+// more waves hide more than the prefetch (2^24 points 51.5 against 51.5 and 52.2
+// against 53.3, 2^25 107 against 100 and 108 against 103; 4096-point rows 211
+// against 214 at 2^26).  Longer rows hold one line per
 // workgroup; their stage twiddles come from factor tables in LDS and the next
 // line is in flight (16384: 69 us against 84 with a table, no line in flight).
 //
@@ -146,8 +150,10 @@ constexpr Pref kPrefs[] = {
     {ROLE_ROW, 32, 128, 8, 16, 0, 0, 0},
     {ROLE_ROW, 32, 256, 8, 8, 0, 0, 0},
     {ROLE_ROW, 32, 512, 8, 4, 0, 0, 0},
+    {ROLE_ROW, 32, 1024, 8, 2, 0, 0, 48 * kCus},
     {ROLE_ROW, 32, 1024, 16, 4, 1, 0, 8 * kCus},
     {ROLE_ROW, 32, 1024, 8, 2, 0, 0, 0},
+    {ROLE_ROW, 32, 2048, 8, 1, 0, 0, 48 * kCus},
     {ROLE_ROW, 32, 2048, 16, 2, 1, 0, 8 * kCus},
     {ROLE_ROW, 32, 2048, 8, 1, 0, 0, 0},
     {ROLE_ROW, 32, 4096, 16, 1, 1, 0, 8 * kCus},
