@@ -76,9 +76,9 @@ _FUSED_ROWS = {256: {4: "f256p8w4q_c64"}, 512: {4: "f512p8w4q_c64"}, 1024: {4: "
                4096: {2: "f4096p16w2q_c64", 4: "f4096p16w4qx_c64"}}
 
 
-def rule_for(shape, dtype):
-    """Schedule string by the shape alone where the planner's own choice of
-    passes is not the fastest, or None."""
+def rule_for(shape, dtype, batch=None):
+    """Schedule string by the shape (and the batch, many images if None) where
+    the planner's own choice of passes is not the fastest, or None."""
     if len(shape) != 2:
         return None
     rows, cols = int(shape[0]), int(shape[1])
@@ -86,10 +86,13 @@ def rule_for(shape, dtype):
     if fused and rows in (2048, 4096, 8192, 16384):
         r = 2 if rows == 2048 and 2 in fused else 4
         return f"rowcol={r};row={fused[r]}"
-    if rows == 4096 and cols > 1:
+    if rows == 4096 and cols > 1 and (batch is None or cols * int(batch) > (128 if dtype == capi.FFT_C64 else 256)):
         # rows, then whole columns: 2^24 points in 16-bit storage 77-91 us
         # against 88-106 in three passes, complex64 with 32 or 128 columns
-        # 127-129 against 138-141
+        # 127-129 against 138-141.  Not where the columns are fewer than give
+        # every other CU a tile: complex64 1 x 32 columns 17.0 against 12.3,
+        # 1 x 128 20.1 against 17.4, 4 x 64 20.4 against 21.0; 16-bit 4 x 64 17.6
+        # against 16.4, 1 x 256 20.0 against 17.0, 4 x 128 21.3 against 23.8
         return "col3=0"
     return None
 
@@ -98,7 +101,7 @@ def schedule_for(shape, batch, dtype):
     """Tuned schedule string for a strided plan, or the rule's, or None."""
     with _lock:
         e = _load_cache().get(_key("plan", shape, batch, dtype))
-    return rule_for(shape, dtype) if e is None else e["schedule"]
+    return rule_for(shape, dtype, batch) if e is None else e["schedule"]
 
 
 def many_schedule_for(sizes, dtype):

@@ -8,7 +8,7 @@ DTYPES = {"c64": capi.FFT_C64, "f16": capi.FFT_C16F, "bf16": capi.FFT_C16BF}
 
 def plan_names(shape, batch, dtype):
     """Variants of the plan the Python layer asks for, without tuned entries."""
-    schedule = autotune.rule_for(shape, dtype) if len(shape) == 2 else None
+    schedule = autotune.rule_for(shape, dtype, batch) if len(shape) == 2 else None
     return tuple(capi.fft_describe(list(shape), batch, len(shape), dtype, schedule)["names"])
 
 

@@ -29,3 +29,13 @@ def test_the_cases_are_the_steps():
     # 1024-point rows in complex64 turn persistent at 2048 tiles of 4 rows
     assert ((1024,), 8188) in planner_cases.lines(capi.FFT_C64)
     assert ((1024,), 8189) in planner_cases.lines(capi.FFT_C64)
+
+
+def test_4096_rows_few_columns_keep_the_three_passes():
+    # from one strip of columns per other CU on: rows, then whole columns
+    for dt, most in (("c64", 128), ("f16", 256), ("bf16", 256)):
+        dtype = planner_cases.DTYPES[dt]
+        for cols in (16, 32, 64, 128):
+            few, many = most // cols, most // cols + 1
+            assert len(planner_cases.plan_names((4096, cols), few, dtype)) == 3
+            assert len(planner_cases.plan_names((4096, cols), many, dtype)) == 2
