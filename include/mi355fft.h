@@ -106,7 +106,8 @@ int fft_plan(const int64_t *n, int64_t batch, int dims, int dtype, int direction
  *                                       Persistent variants ('q'): the workgroups
  *                                       of one XCD start on consecutive tiles.
  *                                       Without the key: 1 for passes whose
- *                                       strips are narrower than a 128 B line)
+ *                                       strips are narrower than a 128 B line and
+ *                                       have neighbours in their batch)
  *             | 'col3=' 0|1           (2-D: columns as two sub-passes of sqrt(rows)
  *                                       points; rows a power of 4, at least 2 columns)
  *             | 'colt=' variant       (the first of those sub-passes)

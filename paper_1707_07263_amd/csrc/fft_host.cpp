@@ -866,10 +866,16 @@ int apply_xcd(const std::string& mask, int dtype, Schedule* S) {
     // strips whose row segments are narrower than a 128-byte line share each
     // line with their neighbours: on one XCD the line is fetched into its L2
     // once (512-point bf16 columns, 16 per tile: 24 us against 34; 4096-point
-    // complex64 columns, 8 per tile: 74 against 85)
-    for (PassSpec& ps : S->passes)
-      ps.args.xcd_remap = ps.v && (ps.v->role == ROLE_SPLIT_A || ps.v->role == ROLE_COL || ps.v->role == ROLE_COL_TW) &&
-                          (size_t)ps.v->W * esize(dtype) < 128;
+    // complex64 columns, 8 per tile: 74 against 85).  A strip that is alone in
+    // its batch shares none, and the placement costs (8192 images of 1024 x 2,
+    // complex64: 109 against 89; 2048 of 1024 x 8: 108 against 93)
+    for (PassSpec& ps : S->passes) {
+      const bool strips =
+          ps.v && (ps.v->role == ROLE_SPLIT_A || ps.v->role == ROLE_COL || ps.v->role == ROLE_COL_TW);
+      // neighbours in the batch, or batches side by side in a row
+      const bool neighbours = ps.args.tiles_per_batch > 1 || ps.args.out_batch <= ps.args.lines;
+      ps.args.xcd_remap = strips && neighbours && (size_t)ps.v->W * esize(dtype) < 128;
+    }
     return FFT_OK;
   }
   if (mask.size() != 1 && mask.size() != n) return FFT_ERR_INVALID_ARGUMENT;
