@@ -123,6 +123,10 @@ size_t esize(int dtype) { return dtype == FFT_C64 ? 8 : 4; }
 // against 214 at 2^26).  Longer rows hold one line per
 // workgroup; their stage twiddles come from factor tables in LDS and the next
 // line is in flight (16384: 69 us against 84 with a table, no line in flight).
+// 16384 points in 16-bit storage: two lines per CU where there are more lines
+// than CUs (257 lines 28 us against 34 in fp16, 26 against 34 in bf16), else
+// one, which fp16 runs faster with 1024 lanes of 16 points (128 lines 17.2 us
+// against 21.1; bf16 17.1 against 16.7).
 //
 // Columns and first passes of a split: as wide as LDS and registers allow
 // while there are tiles for every CU (two for every CU where a tile of 32
@@ -140,6 +144,7 @@ struct Pref {
   int role, bits, L;  // bits: storage of one component, 32 or 16
   int P, W, persistent, ex;
   int64_t min_tiles;
+  int dtype = -1;  // this storage type only
 };
 constexpr int64_t kCus = 256;  // MI355X
 constexpr int64_t kMaxLanes = UINT32_MAX;  // of one launch
@@ -170,6 +175,8 @@ constexpr Pref kPrefs[] = {
     {ROLE_ROW, 16, 2048, 8, 1, 0, 0, 0},
     {ROLE_ROW, 16, 4096, 8, 1, 0, 0, 0},
     {ROLE_ROW, 16, 8192, 8, 1, 0, 0, 0},
+    {ROLE_ROW, 16, 16384, 32, 1, 0, 1, kCus + 1},
+    {ROLE_ROW, 16, 16384, 16, 1, 0, 0, 0, FFT_C16F},
     {ROLE_ROW, 16, 16384, 32, 1, 0, 1, 0},
 
     {ROLE_SPLIT_A, 32, 128, 8, 32, 0, 0, 2 * kCus},
@@ -257,6 +264,7 @@ constexpr Pref kPrefs[] = {
 const Variant* preferred(int role, int L, int dtype, int want_w, int64_t lines, int64_t batches) {
   for (const Pref& f : kPrefs) {
     if (f.role != role || f.L != L || f.bits != (dtype == FFT_C64 ? 32 : 16)) continue;
+    if (f.dtype >= 0 && f.dtype != dtype) continue;
     if (role != ROLE_ROW && f.W > lines) continue;
     if ((lines + f.W - 1) / f.W * batches < f.min_tiles) continue;
     for (const Variant& v : variants())

@@ -39,3 +39,10 @@ def test_4096_rows_few_columns_keep_the_three_passes():
             few, many = most // cols, most // cols + 1
             assert len(planner_cases.plan_names((4096, cols), few, dtype)) == 3
             assert len(planner_cases.plan_names((4096, cols), many, dtype)) == 2
+
+
+def test_16384_point_rows_by_lines_per_cu():
+    # one line per CU and more: fp16 changes its lanes, bf16 does not
+    for dt, few in (("f16", "r16384p16w1_f16"), ("bf16", "r16384p32w1x_bf16")):
+        names = [planner_cases.plan_names((16384,), b, planner_cases.DTYPES[dt]) for b in (1, 256, 257, 1024)]
+        assert names == [(few,), (few,), (f"r16384p32w1x_{dt}",), (f"r16384p32w1x_{dt}",)]
