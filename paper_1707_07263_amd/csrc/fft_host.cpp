@@ -261,22 +261,28 @@ constexpr Pref kPrefs[] = {
 // The preferred variant of a pass over `batches` sets of `lines` lines, or
 // the general choice of pick() for lengths the table leaves out and for fewer
 // lines than its tiles are wide.  Contiguous lines may be fewer than a tile.
+// Where every variant is wider than the lines, the table's narrowest if that
+// is narrower than pick()'s (fp16, 1024 x 2 by 8192 images: 8 columns per tile
+// 114 us, 16 253; 512 x 2 by 16384: 92 and 198).
 const Variant* preferred(int role, int L, int dtype, int want_w, int64_t lines, int64_t batches) {
+  const Variant* narrow = nullptr;
   for (const Pref& f : kPrefs) {
     if (f.role != role || f.L != L || f.bits != (dtype == FFT_C64 ? 32 : 16)) continue;
     if (f.dtype >= 0 && f.dtype != dtype) continue;
-    if (role != ROLE_ROW && f.W > lines) continue;
-    if ((lines + f.W - 1) / f.W * batches < f.min_tiles) continue;
+    const bool wide = role != ROLE_ROW && f.W > lines;
+    if (!wide && (lines + f.W - 1) / f.W * batches < f.min_tiles) continue;
     for (const Variant& v : variants())
       if (v.role == role && v.L == L && v.dtype == dtype && v.P == std::min(f.P, L) && v.W == f.W &&
           v.persistent == f.persistent && v.ex == f.ex) {
         // 8 points per lane are too few from 2^35 points on (128 GiB in
         // 16-bit storage): the general choice has 16
         if (!v.persistent && (lines + v.W - 1) / v.W * batches > kMaxLanes / v.threads) break;
-        return &v;
+        if (!wide) return &v;
+        if (!narrow || v.W < narrow->W) narrow = &v;
       }
   }
-  return pick(role, L, dtype, want_w, lines);
+  const Variant* general = pick(role, L, dtype, want_w, lines);
+  return general && narrow && general->W > lines && narrow->W < general->W ? narrow : general;
 }
 
 // ---------------------------------------------------------------------------

@@ -46,3 +46,16 @@ def test_16384_point_rows_by_lines_per_cu():
     for dt, few in (("f16", "r16384p16w1_f16"), ("bf16", "r16384p32w1x_bf16")):
         names = [planner_cases.plan_names((16384,), b, planner_cases.DTYPES[dt]) for b in (1, 256, 257, 1024)]
         assert names == [(few,), (few,), (f"r16384p32w1x_{dt}",), (f"r16384p32w1x_{dt}",)]
+
+
+def test_fewer_columns_than_any_tile_take_the_narrowest():
+    # 16-bit columns have no tiles of 2 or 4: no more than half a tile idle
+    # where a narrower one exists
+    for dt in ("f16", "bf16"):
+        dtype = planner_cases.DTYPES[dt]
+        for rows, width in ((256, 8), (512, 8), (1024, 8), (2048, 4), (4096, 4)):
+            for cols in (2, 4):
+                for batch in (1, 64, 1024):
+                    names = planner_cases.plan_names((rows, cols), batch, dtype)
+                    d = {capi.fft_variant_name(i): i for i in range(capi.fft_variant_count())}
+                    assert capi.fft_variant_describe(d[names[-1]])["W"] == width, names
