@@ -161,7 +161,9 @@ int fft_plan_ex(const int64_t *n, int64_t batch, int dims, int dtype, int direct
  * in two launches: the first runs every one-pass transform and the first pass
  * of every two-pass one, the second (skipped if there is none) every second
  * pass, so the kernel boundary orders each transform's passes (Sec. 2.3.3).
- * By default every tile is a workgroup of its own.  The persistent kernels of
+ * By default every tile is a workgroup of its own, except where long lengths
+ * hold most of the points (2^18 and more; fft_plan_info names the kernel): those
+ * run by the persistent 'pipe=2'.  The persistent kernels of
  * the schedule string below claim their tiles from a device queue: 'pipe=2' in
  * the same two launches, 'pipe=0|1' in one, chaining a transform's passes by a
  * completion counter.  Their queue state lives in the plan's workspace and is
@@ -175,7 +177,8 @@ int fft_plan_many(const int64_t *sizes, int64_t count, int dtype, int direction,
 /*
  * As fft_plan_many with a schedule string of ';'-separated items.  A string
  * with none of p, threads, pipe, lag, ntst and ntail plans the default kernel,
- * one workgroup of 512 lanes with 8 points each per tile.
+ * one workgroup of 512 lanes with 8 points each per tile, or 'pipe=2' where the
+ * lengths are mostly long.
  *   'flat=1'           that kernel by name (with none of the six)
  *   'p=' 8|16          points per lane (radix of the in-register stages)
  *   'threads=' 256|512 workgroup size (not every dtype has every size;

@@ -29,6 +29,9 @@ class Plan:
         # two-launch kernels never wait)
         self.waits = kind == "many" and capi.fft_plan_info(handle)["pass_variant"][0] not in ("many_flat",
                                                                                                "many_2launch")
+        # batched plans of the queue kernel by the planner's rule: their queue
+        # state is each call's own, so that calls on several streams may overlap
+        self.own_queue = 0
         # fused 2-D plans run in place without scratch; with it they save the
         # pass that orders the rows
         self.optional_scratch = 0
@@ -49,11 +52,13 @@ class Plan:
             if not x.is_cuda:
                 raise ValueError("input must be a GPU tensor where no stream is given")
             stream = _raw_stream(x.device.index)
-            if self.optional_scratch and self.workspace is None and x.data_ptr() == out.data_ptr():
-                scratch = _scratch(self.optional_scratch, x.device)
+            nbytes = self.own_queue
+            if self.optional_scratch and x.data_ptr() == out.data_ptr():
+                nbytes = self.optional_scratch
+            if nbytes and self.workspace is None:
+                scratch = _scratch(nbytes, x.device)
                 if scratch is not None:
-                    capi.fft_exec_ws(self.handle, x.data_ptr(), out.data_ptr(), stream, scratch.data_ptr(),
-                                     self.optional_scratch)
+                    capi.fft_exec_ws(self.handle, x.data_ptr(), out.data_ptr(), stream, scratch.data_ptr(), nbytes)
                     return
         capi.fft_exec(self.handle, x.data_ptr(), out.data_ptr(), stream)
 
@@ -139,8 +144,10 @@ def get_plan(shape, batch: int, dtype: int, direction: int, *, scale=None,
 def get_many_plan(sizes, dtype: int, direction: int, *, scale=None, schedule=None,
                   device=None) -> Plan:
     dev = torch.cuda.current_device() if device is None else torch.device(device).index
+    ruled = False
     if schedule is None:
         schedule = autotune.many_schedule_for(sizes, dtype)
+        ruled = schedule is None
     key = ("many", tuple(int(s) for s in sizes), dtype, direction, scale, schedule, dev)
     with _lock:
         p = _cache.get(key)
@@ -148,6 +155,8 @@ def get_many_plan(sizes, dtype: int, direction: int, *, scale=None, schedule=Non
             with torch.cuda.device(dev):
                 h = capi.fft_plan_many_ex([int(s) for s in sizes], dtype, direction, schedule)
                 p = Plan(h, "many")
+                if ruled and p.info()["pass_variant"][0] == "many_2launch":
+                    p.own_queue = capi.fft_workspace_size(h)
                 if scale is not None:
                     p.set_scale(scale)
             _cache[key] = p

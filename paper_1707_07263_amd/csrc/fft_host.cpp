@@ -1873,6 +1873,28 @@ void split_launches(ManyBuild* mb) {
   mb->q_off[2] = (int32_t)mb->items.size();
 }
 
+// What the plain-grid kernel's second tiles and narrow strips cost against the
+// pipelined two-launch kernel, in microseconds, beyond its start: its tiles
+// hold 4096 points, so from 2^18 on their strips are 8, 4, 2 and 1 columns wide
+// (complex64: 64 bytes and less), half of the other kernel's, and strips that
+// do not start on a line (behind transforms of fewer than 128 bytes) touch one
+// line more each.  Measured per 2^20 points (uniform lengths): complex64 2^18
+// 4 x 18 against 27 us, 16 x 45 and 45, 64 x 143 and 130; 2^20 1 x 28 and 30, 4 x
+// 72 and 54, 16 x 245 and 147; 2^22 135 and 76; 160 mixed lengths 2^0 .. 2^20
+// 240 and 166, 2000 of 2^0 .. 2^16 118 and 108.  16-bit storage, whose passes
+// are bound by instructions: 2^20 4 x 46 and 53, 16 x 147 and 137; 2^22 88 and 73;
+// the mixed 160 160 and 140.
+double flat_excess_us(int lg, int64_t n, bool aligned, int dtype) {
+  static constexpr double kWide[] = {0.4, 1.0, 3.0, 6.8, 8.0, 11.5, 14.4};  // 2^16 ..
+  const double m = (double)n / (1 << 20);
+  if (dtype == FFT_C64) return m * ((lg < 16 ? 0 : kWide[std::min(lg - 16, 6)]) + (aligned ? 0 : 1.5));
+  return m * ((lg < 20 ? 0 : lg < 22 ? 1.4 : 8.0) + (aligned || lg < 17 ? 0 : 2.5));
+}
+// and what the other kernel's prologue (stage twiddles into LDS, a drained
+// first load) takes longer than the plain grid, with the clearing of queue
+// state that an exec brings along
+constexpr double kFlatStartUs = 15.0;
+
 // Host-only part of a batched plan: per-transform descriptors, the ordered
 // work queue and the one-pass groups.  No GPU calls.
 int build_many(const int64_t* sizes, int64_t count, int dtype, int direction, const char* schedule,
@@ -1897,6 +1919,7 @@ int build_many(const int64_t* sizes, int64_t count, int dtype, int direction, co
   xf.assign((size_t)count, ManyXform{});
   std::vector<int> lgs((size_t)count);
   int64_t off = 0;
+  double excess = 0;
   for (int64_t i = 0; i < count; ++i) {
     const int64_t n = sizes[i];
     if (!pow2(n) || ilog2_64(n) > FFT_MAX_LOG2_1D) return FFT_ERR_UNSUPPORTED_SIZE;
@@ -1925,6 +1948,7 @@ int build_many(const int64_t* sizes, int64_t count, int dtype, int direction, co
       const int wa = tile_lines(x.lg1, opt.P, opt.threads);
       x.nA = (int32_t)((N2 + wa - 1) / wa);
       mb->pass_points += 2 * n;
+      excess += flat_excess_us(lg, n, off * (int64_t)esize(dtype) % 128 == 0, dtype);
     } else {
       mb->pass_points += n;
     }
@@ -1993,15 +2017,18 @@ int build_many(const int64_t* sizes, int64_t count, int dtype, int direction, co
   while (b_next < split_ids.size()) push_b(split_ids[b_next++]);
   if (items.size() > (size_t)INT32_MAX / 2) return FFT_ERR_UNSUPPORTED_SIZE;
   if (opt.pipe >= 2) split_launches(mb);
-  if (opt.pipe == 3 && std::max(mb->q_off[1], mb->q_off[2] - mb->q_off[1]) > kMaxLanes / opt.threads) {
+  if (opt.pipe == 3) {
     // more tiles than one launch takes (2^35 points and more): the persistent
     // kernel, whose grid does not grow with them
-    if (opt.flat) return FFT_ERR_UNSUPPORTED_SIZE;
-    ManyBuild queue;
-    const std::string s = (schedule && *schedule ? std::string(schedule) + ";" : std::string()) + "pipe=2";
-    const int rc = build_many(sizes, count, dtype, direction, s.c_str(), &queue);
-    if (!rc) *mb = std::move(queue);
-    return rc;
+    const bool too_many = std::max(mb->q_off[1], mb->q_off[2] - mb->q_off[1]) > kMaxLanes / opt.threads;
+    if (opt.flat) return too_many ? FFT_ERR_UNSUPPORTED_SIZE : FFT_OK;
+    if (too_many || excess > kFlatStartUs) {
+      ManyBuild queue;
+      const std::string s = (schedule && *schedule ? std::string(schedule) + ";" : std::string()) + "pipe=2";
+      const int rc = build_many(sizes, count, dtype, direction, s.c_str(), &queue);
+      if (!rc) *mb = std::move(queue);
+      return rc;
+    }
   }
   return FFT_OK;
 }
