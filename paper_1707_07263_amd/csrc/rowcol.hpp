@@ -77,13 +77,16 @@ __global__ void __launch_bounds__((W * Sched<L, P>::T), 1) k_rowcol(PassArgs a) 
     const int64_t b = tl >> lgM;
     const int64_t n1 = tl & (M - 1);
     const int m = tid / T, t = tid % T;
-    const TS* src = reinterpret_cast<const TS*>(a.in) + b * a.in_batch + n1 * a.in_line + m * a.in_elem + t;
+    // a base of the workgroup and a 32-bit offset of the lane (an image has at
+    // most 2^28 points)
+    const TS* src = reinterpret_cast<const TS*>(a.in) + b * a.in_batch + n1 * a.in_line;
+    const uint32_t off = (uint32_t)m * (uint32_t)a.in_elem + (uint32_t)t;
 #pragma unroll
     for (int q = 0; q < PP; ++q) {
       if constexpr (sizeof(TS) == 8)
-        vn[q] = load_stream(reinterpret_cast<const float2*>(src + q * T));
+        vn[q] = load_stream(reinterpret_cast<const float2*>(src + (off + q * T)));
       else
-        vn[q] = src[q * T];
+        vn[q] = src[off + q * T];
     }
     // W_R^{n1 k2}, k2 < W (n1 k2 < M W = R)
 #pragma unroll
