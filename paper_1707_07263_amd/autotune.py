@@ -318,6 +318,46 @@ def tune_plan(shape, batch, dtype=capi.FFT_C64, reps=10, verbose=False):
     return best[1] or "", best[2]
 
 
+# In 16-bit storage a second pass rounds once more, so that a faster schedule
+# would be a less accurate one: lengths that fit a tile keep their one pass.
+def _one_pass_kept(dtype):
+    return dtype != capi.FFT_C64
+
+
+def _many_grid(dtype):
+    """Global schedules of a batched plan that the tuner times."""
+    grid = []
+    for P in (8, 16):
+        for threads in (256, 512):
+            for pipe in (0, 1):
+                # the pipelined kernel keeps tiles up to 2^12 (512 lanes) or 2^11
+                max_tile = min(12 if (not pipe or threads == 512) else 11, int(math.log2(threads * P)))
+                if _one_pass_kept(dtype) and max_tile < 12:
+                    continue
+                for pass2 in range(max_tile + 1 if _one_pass_kept(dtype) else max(8, max_tile - 3), max_tile + 2):
+                    for order in ("bigfirst", "given"):
+                        grid.append(f"p={P};threads={threads};pass2={pass2};order={order}"
+                                    + (";pipe=1" if pipe else ";pipe=0"))
+    # the plain-grid kernel, and the two-launch persistent one (512 lanes,
+    # tiles up to 2^12)
+    for kernel in ("flat=1", "p=16;threads=512;pipe=2"):
+        for pass2 in range(13 if _one_pass_kept(dtype) else 9, 14):
+            grid.append(f"{kernel};pass2={pass2}")
+    return grid
+
+
+def _length_options(lg, pass2, max_tile, dtype):
+    """Choices for one length: one pass or two, and the first-pass length."""
+    options = []
+    if lg <= max_tile and _one_pass_kept(dtype):
+        return options
+    if lg <= max_tile and lg >= 2:
+        options.append(("pass", 1 if lg >= pass2 else 2))
+    for l1 in range(max(1, lg - max_tile), min(max_tile, lg - 1) + 1):
+        options.append(("n1", l1))
+    return options
+
+
 def tune_many(sizes, dtype=capi.FFT_C64, reps=10, verbose=False):
     """Tune a batched-uneven plan; returns (schedule string, microseconds)."""
     import torch
@@ -338,22 +378,7 @@ def tune_many(sizes, dtype=capi.FFT_C64, reps=10, verbose=False):
             print(f"  {per[0]:9.2f} us  {s}", flush=True)
         return per[0]
 
-    grid = []
-    for P in (8, 16):
-        for threads in (256, 512):
-            for pipe in (0, 1):
-                # the pipelined kernel keeps tiles up to 2^12 (512 lanes) or 2^11
-                max_tile = min(12 if (not pipe or threads == 512) else 11, int(math.log2(threads * P)))
-                for pass2 in range(max(8, max_tile - 3), max_tile + 2):
-                    for order in ("bigfirst", "given"):
-                        grid.append(f"p={P};threads={threads};pass2={pass2};order={order}"
-                                    + (";pipe=1" if pipe else ";pipe=0"))
-    # the plain-grid kernel, and the two-launch persistent one (512 lanes,
-    # tiles up to 2^12)
-    for pass2 in range(9, 14):
-        grid.append(f"flat=1;pass2={pass2}")
-    for pass2 in range(9, 14):
-        grid.append(f"p=16;threads=512;pipe=2;pass2={pass2}")
+    grid = _many_grid(dtype)
     best = None
     for s in grid:
         us = timed(s)
@@ -367,7 +392,7 @@ def tune_many(sizes, dtype=capi.FFT_C64, reps=10, verbose=False):
             if us is not None and us < best[0]:
                 best = (us, f"{base};lag={lag}")
     if best is not None:
-        best = _tune_per_length(sizes, best, timed)
+        best = _tune_per_length(sizes, best, timed, dtype)
     if best is not None and "pipe=2" in best[1]:
         # nontemporal stores for the last items of each launch
         base = best[1]
@@ -378,7 +403,7 @@ def tune_many(sizes, dtype=capi.FFT_C64, reps=10, verbose=False):
     return best[1], [best[0]]
 
 
-def _tune_per_length(sizes, best, timed):
+def _tune_per_length(sizes, best, timed, dtype):
     """Per-length choices on top of the best global schedule: for every
     length present, one pass or two (where both are possible) and, for two
     passes, the first-pass length N1 (coordinate descent, two sweeps, each
@@ -394,12 +419,7 @@ def _tune_per_length(sizes, best, timed):
     cur = dict()
     for _ in range(2):
         for lg in lgs:
-            two_default = lg >= pass2 or lg > max_tile
-            options = []
-            if lg <= max_tile and lg >= 2:
-                options.append(("pass", 1 if two_default else 2))
-            for l1 in range(max(1, lg - max_tile), min(max_tile, lg - 1) + 1):
-                options.append(("n1", l1))
+            options = _length_options(lg, pass2, max_tile, dtype)
             for key, val in options:
                 trial = dict(cur)
                 trial.pop(("pass", lg), None)
