@@ -220,7 +220,11 @@ def _run(x, ndim_fft, inverse, scale, out, schedule):
 
 def fft(x: torch.Tensor, inverse: bool = False, *, scale: float | None = None,
         out: torch.Tensor | None = None, schedule: str | None = None) -> torch.Tensor:
-    """1-D transform along the last axis (eq. 1; with inverse=True eq. 2)."""
+    """1-D transform along the last axis (eq. 1; with inverse=True eq. 2).
+
+    In place (``out=x``), lengths that take two passes (2^15 to 2^24) go
+    through scratch that the plan keeps: such calls of one shape must not
+    overlap on several streams.  Out of place they may."""
     return _run(x, 1, inverse, scale, out, schedule)
 
 
@@ -230,7 +234,8 @@ def ifft(x: torch.Tensor, **kw) -> torch.Tensor:
 
 def fft2(x: torch.Tensor, inverse: bool = False, *, scale: float | None = None,
          out: torch.Tensor | None = None, schedule: str | None = None) -> torch.Tensor:
-    """2-D transform over the last two axes: rows, then columns."""
+    """2-D transform over the last two axes: rows, then columns.  In place
+    too, on any streams."""
     return _run(x, 2, inverse, scale, out, schedule)
 
 

@@ -1873,26 +1873,24 @@ void split_launches(ManyBuild* mb) {
   mb->q_off[2] = (int32_t)mb->items.size();
 }
 
-// What the plain-grid kernel's second tiles and narrow strips cost against the
-// pipelined two-launch kernel, in microseconds, beyond its start: its tiles
-// hold 4096 points, so from 2^18 on their strips are 8, 4, 2 and 1 columns wide
-// (complex64: 64 bytes and less), half of the other kernel's, and strips that
-// do not start on a line (behind transforms of fewer than 128 bytes) touch one
-// line more each.  Measured per 2^20 points (uniform lengths): complex64 2^18
-// 4 x 18 against 27 us, 16 x 45 and 45, 64 x 143 and 130; 2^20 1 x 28 and 30, 4 x
-// 72 and 54, 16 x 245 and 147; 2^22 135 and 76; 160 mixed lengths 2^0 .. 2^20
-// 240 and 166, 2000 of 2^0 .. 2^16 118 and 108.  16-bit storage, whose passes
-// are bound by instructions: 2^20 4 x 46 and 53, 16 x 147 and 137; 2^22 88 and 73;
-// the mixed 160 160 and 140.
+// What the plain-grid kernel takes longer than the pipelined two-launch one, in
+// microseconds, beyond its shorter start.  Its tiles hold 4096 points, half of
+// the other's, and so do its strips: from 2^18 points on they are 8, 4, 2 and 1
+// columns wide (complex64: 64 bytes and less), and strips that do not start on
+// a line, behind transforms of fewer than 128 bytes, touch one line more each.
+// Measured, plain grid and queue: complex64 2^18 4 x 18 and 27 us, 16 x 45 and
+// 45, 64 x 143 and 130; 2^20 1 x 28 and 30, 4 x 72 and 54, 16 x 245 and 147; 2^22
+// 135 and 76; 160 mixed lengths 2^0 .. 2^20 240 and 166, 2000 of 2^0 .. 2^16 118 and
+// 108.  16-bit storage, whose passes are bound by instructions: 2^20 4 x 46 and
+// 53, 16 x 147 and 137; 2^22 88 and 73; the mixed 160 160 and 140.
 double flat_excess_us(int lg, int64_t n, bool aligned, int dtype) {
   static constexpr double kWide[] = {0.4, 1.0, 3.0, 6.8, 8.0, 11.5, 14.4};  // 2^16 ..
   const double m = (double)n / (1 << 20);
   if (dtype == FFT_C64) return m * ((lg < 16 ? 0 : kWide[std::min(lg - 16, 6)]) + (aligned ? 0 : 1.5));
   return m * ((lg < 20 ? 0 : lg < 22 ? 1.4 : 8.0) + (aligned || lg < 17 ? 0 : 2.5));
 }
-// and what the other kernel's prologue (stage twiddles into LDS, a drained
-// first load) takes longer than the plain grid, with the clearing of queue
-// state that an exec brings along
+// The start that the plain grid saves: a prologue (stage twiddles into LDS, a
+// drained first load) and the clearing of queue state that an exec brings along.
 constexpr double kFlatStartUs = 15.0;
 
 // Host-only part of a batched plan: per-transform descriptors, the ordered
