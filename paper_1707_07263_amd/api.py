@@ -222,9 +222,9 @@ def fft(x: torch.Tensor, inverse: bool = False, *, scale: float | None = None,
         out: torch.Tensor | None = None, schedule: str | None = None) -> torch.Tensor:
     """1-D transform along the last axis (eq. 1; with inverse=True eq. 2).
 
-    In place (``out=x``), lengths that take two passes (2^15 to 2^24) go
+    Lengths of 2^15 to 2^24 in place (``out=x``), and longer ones always, go
     through scratch that the plan keeps: such calls of one shape must not
-    overlap on several streams.  Out of place they may."""
+    overlap on several streams."""
     return _run(x, 1, inverse, scale, out, schedule)
 
 
