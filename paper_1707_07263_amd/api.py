@@ -29,14 +29,14 @@ class Plan:
         # two-launch kernels never wait)
         self.waits = kind == "many" and capi.fft_plan_info(handle)["pass_variant"][0] not in ("many_flat",
                                                                                                "many_2launch")
-        # batched plans of the queue kernel by the planner's rule: their queue
-        # state is each call's own, so that calls on several streams may overlap
-        self.own_queue = 0
-        # fused 2-D plans run in place without scratch; with it they save the
-        # pass that orders the rows
-        self.optional_scratch = 0
+        # bytes of scratch that an exec brings: fused 2-D plans run in place
+        # without, and with it save the pass that orders the rows; batched
+        # plans of the queue kernel by the planner's rule take their queue
+        # state with each call, so that calls on several streams may overlap
+        self.scratch = 0
+        self.scratch_always = False
         if kind == "strided" and capi.fft_plan_info(handle)["pass_variant"][0].startswith("f"):
-            self.optional_scratch = capi.fft_workspace_size(handle)
+            self.scratch = capi.fft_workspace_size(handle)
 
     def __del__(self):
         try:
@@ -49,16 +49,16 @@ class Plan:
 
     def exec(self, x: torch.Tensor, out: torch.Tensor, stream: int | None = None) -> None:
         if stream is None:
-            if not x.is_cuda:
-                raise ValueError("input must be a GPU tensor where no stream is given")
-            stream = _raw_stream(x.device.index)
-            nbytes = self.own_queue
-            if self.optional_scratch and x.data_ptr() == out.data_ptr():
-                nbytes = self.optional_scratch
-            if nbytes and self.workspace is None:
-                scratch = _scratch(nbytes, x.device)
-                if scratch is not None:
-                    capi.fft_exec_ws(self.handle, x.data_ptr(), out.data_ptr(), stream, scratch.data_ptr(), nbytes)
+            try:
+                stream = _raw_stream(x.device.index)
+            except (TypeError, RuntimeError):
+                if x.is_cuda:
+                    raise
+                raise ValueError("input must be a GPU tensor where no stream is given") from None
+            if self.scratch and self.workspace is None and (self.scratch_always or x.data_ptr() == out.data_ptr()):
+                ws = _scratch(self.scratch, x.device)
+                if ws is not None:
+                    capi.fft_exec_ws(self.handle, x.data_ptr(), out.data_ptr(), stream, ws.data_ptr(), self.scratch)
                     return
         capi.fft_exec(self.handle, x.data_ptr(), out.data_ptr(), stream)
 
@@ -100,7 +100,7 @@ _lock = threading.Lock()
 # the current stream's handle of a device by index: without building a
 # torch.cuda.Stream where this torch has the function for it (0.1 us against 1.9)
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
-    lambda index: torch.cuda.current_stream(index).cuda_stream)
+    lambda index: torch.cuda.current_stream(int(index)).cuda_stream)
 
 # Plans by call signature: a repeated call finds its plan with one lookup,
 # where checking the shape, looking the tuned schedule up and building the
@@ -156,7 +156,7 @@ def get_many_plan(sizes, dtype: int, direction: int, *, scale=None, schedule=Non
                 h = capi.fft_plan_many_ex([int(s) for s in sizes], dtype, direction, schedule)
                 p = Plan(h, "many")
                 if ruled and p.info()["pass_variant"][0] == "many_2launch":
-                    p.own_queue = capi.fft_workspace_size(h)
+                    p.scratch, p.scratch_always = capi.fft_workspace_size(h), True
                 if scale is not None:
                     p.set_scale(scale)
             _cache[key] = p
@@ -212,7 +212,7 @@ def _run(x, ndim_fft, inverse, scale, out, schedule):
         out = torch.empty_like(x)
     elif out.shape != x.shape or out.dtype != x.dtype or not out.is_contiguous():
         raise ValueError("out must be a contiguous tensor of the input's shape and dtype")
-    if out.data_ptr() == x.data_ptr() and not plan.optional_scratch:
+    if out.data_ptr() == x.data_ptr() and not plan.scratch:
         plan.ensure_workspace(x.device)
     plan.exec(x, out)
     return out
